@@ -4,13 +4,14 @@
 // Per conv group g the GEMM is  Y^T[m, px] = sum_k Wc_g[m, k] * Xcol[px, k]
 // with px = (n, p, q) an output pixel and k a kept (tap, channel) column.
 // structadmm_conv_fwd takes one of three paths per group, all on MFMA
-// v_mfma_f32_32x32x16_bf16 (A = Wc rows, B = output pixels, fp32 accumulate;
-// small ragged filter groups over a few hundred columns take the 16-row
-// variant of the direct path in conv_ig.hip):
+// bf16 MFMAs (A = Wc rows, B = output pixels, fp32 accumulate):
 //
-// k_conv (direct): the group's columns are every tap times one run of 8k
-//   input channels (dense, filter- or channel-pruned layers); 128-pixel tiles
-//   of 128 or 64 filters with eight wavefronts.  B rows are read
+// direct: the group's columns are every tap times one run of 8k input channels
+//   (dense, filter- or channel-pruned layers).  Most layers run k_conv_tile
+//   (conv_tile.hip); small ragged filter groups over a few hundred columns take
+//   the 16-row kernel of conv_ig.hip; k_conv below stays for layers of few
+//   slices and many tiles (run_conv).
+// k_conv: 128-pixel tiles of 128 or 64 filters with eight wavefronts.  B rows are read
 //   as 16-byte vectors straight from the NHWC input; both operand tiles are
 //   staged through LDS in two buffers of 64 columns (loads of slice s+2 in
 //   flight while slice s is multiplied); raw buffer loads with 32-bit offsets
@@ -39,7 +40,9 @@
 #include <tuple>
 #include <utility>
 
+#include "conv_args.h"
 #include "conv_ig.h"
+#include "conv_tile.h"
 #include "sa_conv_device.h"
 #include "sa_device.h"
 #include "sa_host.h"
@@ -53,31 +56,10 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kBK = 64;            // K slice per stage (= compacted row padding)
 constexpr int kRow = kBK + 8;      // LDS row of a staged operand tile (bf16 elements)
 constexpr int kLdsBytes = 160 * 1024;
 
 // ---------------------------------------------------------------- k_conv
-// One conv group of a launch (every group of a layer runs in one launch).
-struct ConvGroup {
-    const uint16_t *X;   // NHWC input, or the group's gathered Xcol rows
-    const uint16_t *Wc;  // group base
-    uint32_t x_bytes;
-    int32_t Cx, M, K, ldk, run, run_base, o_off, mtiles, begin;
-    FastDiv divRun;
-};
-struct ConvArgs {
-    uint16_t *Y;
-    float *part;          // split K: binary32 partial sums [ksplit][part_stride]
-    int64_t part_stride;  // floats per chunk (N*P*Q*Cy rounded up to 4)
-    int32_t ksplit, base_blocks;
-    int32_t H, W, D, stride, pad, P, Q, NPQ, Cy;
-    int32_t ldy;  // Y's row pitch (>= Cy)
-    int32_t ngroups, nblocks;
-    FastDiv divPQ, divQ, divD, divCy;
-    ConvGroup g[SA_MAX_CONV_GROUPS];
-};
-
 template <int BM, int BN, int WN, int WM>
 struct ConvCfg {
     static constexpr int NT = 64 * WN * WM;
@@ -91,7 +73,7 @@ struct ConvCfg {
     static_assert(TM >= 1 && TN >= 1 && WTM % 32 == 0 && WTN % 32 == 0, "tile shape");
 };
 
-template <int BM, int BN, int WN, int WM, bool SPLIT>
+template <int BM, int BN, int WN, int WM>
 __global__ __launch_bounds__(64 * WN * WM) void k_conv(ConvArgs a) {
     using Cfg = ConvCfg<BM, BN, WN, WM>;
     constexpr int NT = Cfg::NT, WTM = Cfg::WTM, WTN = Cfg::WTN, TM = Cfg::TM, TN = Cfg::TN;
@@ -107,23 +89,13 @@ __global__ __launch_bounds__(64 * WN * WM) void k_conv(ConvArgs a) {
 
     int bid = blockIdx.x;
     bid = xcd_remap(bid, a.nblocks);
-    int chunk = 0;  // split K: the chunk of column slices this workgroup sums
-    if constexpr (SPLIT) {
-        chunk = bid / a.base_blocks;
-        bid -= chunk * a.base_blocks;
-    }
     int gi = 0;
     while (gi + 1 < a.ngroups && bid >= a.g[gi + 1].begin) ++gi;
     const ConvGroup &G = a.g[gi];
     const int lb = bid - G.begin;
     const int mt = lb % G.mtiles, nt = lb / G.mtiles;
     const int m0 = mt * BN, n0 = nt * BM;
-    int s_begin = 0, s_end = G.ldk / kBK;
-    if constexpr (SPLIT) {
-        const int nst = s_end;
-        s_begin = nst * chunk / a.ksplit;
-        s_end = nst * (chunk + 1) / a.ksplit;
-    }
+    const int nst = G.ldk / kBK;
     const int kc = tid & 7, rb = tid >> 3;
     const int frow = lane & 31, fk = (lane >> 5) * 8;
 
@@ -198,16 +170,16 @@ __global__ __launch_bounds__(64 * WN * WM) void k_conv(ConvArgs a) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-    load_stage(s_begin);
+    load_stage(0);
     store_stage(0);
-    if (s_begin + 1 < s_end) load_stage(s_begin + 1);
+    if (1 < nst) load_stage(1);
     __syncthreads();
 
-    for (int s = s_begin; s < s_end; ++s) {
-        if (s + 1 < s_end) store_stage((s + 1 - s_begin) & 1);
-        if (s + 2 < s_end) load_stage(s + 2);
-        const uint16_t *A = sA + ((s - s_begin) & 1) * BN * kRow;
-        const uint16_t *B = sB + ((s - s_begin) & 1) * BM * kRow;
+    for (int s = 0; s < nst; ++s) {
+        if (s + 1 < nst) store_stage((s + 1) & 1);
+        if (s + 2 < nst) load_stage(s + 2);
+        const uint16_t *A = sA + (s & 1) * BN * kRow;
+        const uint16_t *B = sB + (s & 1) * BM * kRow;
 #pragma unroll
         for (int kk = 0; kk < kBK; kk += 16) {
             bf16x8 af[TM], bfr[TN];
@@ -227,24 +199,6 @@ __global__ __launch_bounds__(64 * WN * WM) void k_conv(ConvArgs a) {
     }
 
     // epilogue: accumulator (i, j, r): m = i*32 + (r/4)*8 + (lane/32)*4 + r%4, px = j*32 + lane%32
-    if constexpr (SPLIT) {  // binary32 partial sums of this chunk; k_splitk_sum adds the chunks
-        float *part = a.part + (int64_t)chunk * a.part_stride;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const int m = m0 + wm * WTM + i * 32 + r4 * 8 + (lane >> 5) * 4;
-                    const int px = n0 + wn * WTN + j * 32 + (lane & 31);
-                    if (px >= a.NPQ) continue;
-                    float *dst = part + (int64_t)px * a.Cy + G.o_off + m;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (m + e < G.M) dst[e] = acc[i][j][r4 * 4 + e];
-                }
-        return;
-    }
     uint16_t *sC = reinterpret_cast<uint16_t *>(smem);  // [BM][BN + 8]
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -1035,8 +989,7 @@ int allow_full_lds(const void *kern) {
 template <int BM, int BN, int WN, int WM>
 int launch_conv(ConvArgs a, hipStream_t stream) {
     using Cfg = ConvCfg<BM, BN, WN, WM>;
-    // blocks of group i: [begin, begin + mtiles * ntiles), m-tiles fastest;
-    // with split K, ksplit copies of that range, one per chunk of slices
+    // blocks of group i: [begin, begin + mtiles * ntiles), m-tiles fastest
     const int ntiles = (a.NPQ + BM - 1) / BM;
     int begin = 0;
     for (int i = 0; i < a.ngroups; ++i) {
@@ -1044,22 +997,19 @@ int launch_conv(ConvArgs a, hipStream_t stream) {
         a.g[i].begin = begin;
         begin += a.g[i].mtiles * ntiles;
     }
-    a.base_blocks = begin;
-    a.nblocks = begin * std::max(1, a.ksplit);
-    auto kern = a.ksplit > 1 ? k_conv<BM, BN, WN, WM, true> : k_conv<BM, BN, WN, WM, false>;
+    a.nblocks = begin;
+    auto kern = k_conv<BM, BN, WN, WM>;
     if (int rc = allow_full_lds(reinterpret_cast<const void *>(kern))) return rc;
     hipLaunchKernelGGL(kern, dim3(a.nblocks), dim3(Cfg::NT), Cfg::lds, stream, a);
     return check_hip(hipGetLastError(), "k_conv");
 }
 
-// Tile shape of the direct kernel for groups of Ms filters over NPQ pixels:
-// 0 = 128 x 128, 1 = 128 x 64 (pixels x filters; eight wavefronts, two
-// workgroups per CU by LDS); *blocks receives the tile count.  The slowest CU runs
-// ceil(tiles / CUs) tiles, and a 128 x 64 tile takes about 3/4 of the time of
-// a 128 x 128 one (0.53-0.87 measured over the ResNet-50 and AlexNet layers,
-// most near 0.75), so 128 x 64 tiles when 3 rounds of them cost no more than
-// 4 rounds of 128 x 128 ones.
-int direct_pick(const int *Ms, int n, int NPQ, int64_t *blocks) {
+// Tiles of 128 pixels that groups of Ms filters over NPQ pixels take in k_conv's
+// shapes: 128 filters each, or 64 when 3 rounds of those over the CUs cost no
+// more than 4 of the wider ones (a 64-filter tile takes about 3/4 of the time
+// of a 128-filter one); *filters receives the choice.  Sets how far a launch
+// may be split (split_plan) and the padding that k_ig is compared with.
+int64_t direct_tiles(const int *Ms, int n, int NPQ, int *filters) {
     int64_t t128 = 0, t64 = 0;
     for (int i = 0; i < n; ++i) {
         t128 += (Ms[i] + 127) / 128;
@@ -1069,22 +1019,15 @@ int direct_pick(const int *Ms, int n, int NPQ, int64_t *blocks) {
     t128 *= ptiles;
     t64 *= ptiles;
     const int64_t r128 = (t128 + cus - 1) / cus, r64 = (t64 + cus - 1) / cus;
-    if (3 * r64 <= 4 * r128) {
-        *blocks = t64;
-        return 1;
-    }
-    *blocks = t128;
-    return 0;
+    *filters = 3 * r64 <= 4 * r128 ? 64 : 128;
+    return *filters == 64 ? t64 : t128;
 }
 
-// One launch for every group of a, in direct_pick's tile shape.  Eight
-// wavefronts per 128-pixel tile (two rows of four, each 32 pixels by 32 or 64
-// filters) keep 16 wavefronts per CU in flight to cover the operand latency:
-// over 94 ResNet-50 layer runs they took 0.73-1.05x (15% less in sum) of the
-// time of four-wavefront tiles of the same size; for groups of at most 32
-// filters 128 x 64 tiles also beat 256 x 32 ones with four wavefronts (CIFAR
-// 3x3 layer of 32 kept filters 12.6 -> 10.0 us, [256,256,3,3] at 10% kept
-// 39.4 -> 30.9 us).
+// One launch for every group of a, by the kernel and tile shape that the time
+// model of conv_tile.hip expects to be fastest: k_conv_tile, or k_conv with
+// eight wavefronts per 128-pixel tile (two rows of four, each 32 pixels by 32
+// or 64 filters) where a layer has few slices and many tiles: its workgroups,
+// two per CU, hide each other's output.
 int run_conv(ConvArgs a, hipStream_t stream) {
     if (a.ngroups == 0) return SA_OK;
     for (int i = 0; i < a.ngroups; ++i)
@@ -1093,12 +1036,11 @@ int run_conv(ConvArgs a, hipStream_t stream) {
     a.divCy = make_fastdiv((uint32_t)std::max(1, a.Cy));
     a.divQ = make_fastdiv((uint32_t)a.Q);
     a.divD = make_fastdiv((uint32_t)a.D);
-    int Ms[SA_MAX_CONV_GROUPS];
-    for (int i = 0; i < a.ngroups; ++i) Ms[i] = a.g[i].M;
-    int64_t blocks;
-    switch (direct_pick(Ms, a.ngroups, a.NPQ, &blocks)) {
-        case 0: return launch_conv<128, 128, 4, 2>(a, stream);
-        default: return launch_conv<128, 64, 4, 2>(a, stream);
+    const int row = a.ksplit > 1 ? kTileSplit : tile_pick(a);
+    switch (row) {
+        case kConv128x128: return launch_conv<128, 128, 4, 2>(a, stream);
+        case kConv128x64: return launch_conv<128, 64, 4, 2>(a, stream);
+        default: return tile_run(a, row, stream);
     }
 }
 
@@ -1264,45 +1206,65 @@ int patch_lds(int TM, int TN, int patch_bytes, int tab_bytes, int NW = 4) {
 // Split K when every group takes the direct kernel (on the input, or on its
 // gathered im2col rows), the launches leave CUs idle and the tiles are long
 // (small batches): the 64-column slices are cut into ksplit chunks (at most 8,
-// at most one workgroup per CU in all), each workgroup writes binary32
+// at most one 128-pixel tile per CU in all), each workgroup writes binary32
 // partial sums, and k_splitk_sum adds them in chunk order.  (The footprint kernel is not split:
 // each of its workgroups copies the whole input footprint, which then
 // dominates; measured slower at batch 1.)
-void split_plan(const sa_compact_sizes &s, ConvPlan *pl) {
+void split_plan(const sa_conv_desc &d, const sa_compact_sizes &s, ConvPlan *pl) {
     ConvPlan &p = *pl;
     p.ksplit = 1;
     int nd = 0, ng = 0, Md[SA_MAX_CONV_GROUPS], Mg[SA_MAX_CONV_GROUPS];
     int min_sl = 1 << 30;
+    ConvArgs a;  // what the time model reads of the direct groups
+    memset(&a, 0, sizeof a);
+    a.C = p.s2d_direct ? p.gC : d.C;
+    a.D = p.s2d_direct ? p.gD : d.D;
+    a.W = p.s2d_direct ? p.gW : d.W;
+    a.pad = p.s2d_direct ? 0 : d.pad;
+    a.NPQ = p.NPQ;
     for (int g = 0; g < s.groups; ++g) {
         if (p.path[g] == kSkip) continue;
         if (p.path[g] == kPatch) return;
-        if (p.path[g] == kDirect)
+        if (p.path[g] == kDirect) {
             Md[nd++] = s.M[g];
-        else  // two-phase: the direct kernel over the gathered rows
+            ConvGroup &G = a.g[a.ngroups++];
+            G.M = s.M[g];
+            G.ldk = s.ldk[g];
+            G.run = s.run[g];
+            G.Cx = p.s2d_direct ? p.gCx : d.Cx;
+            G.x_bytes = (uint32_t)(p.s2d_direct ? p.s2d_bytes : (size_t)d.N * d.H * d.W * d.Cx * 2);
+        } else {  // two-phase: the direct kernel over the gathered rows
             Mg[ng++] = s.M[g];
+        }
         min_sl = std::min(min_sl, s.ldk[g] / kBK);
     }
     if (nd + ng == 0) return;
-    int64_t base = 0, b;
-    if (nd > 0) {
-        direct_pick(Md, nd, p.NPQ, &b);
-        base += b;
-    }
-    if (ng > 0) {
-        direct_pick(Mg, ng, p.NPQ, &b);
-        base += b;
-    }
-    // the columns split over ks workgroups per tile only while the tiles
-    // leave CUs idle (ks <= CUs / tiles: one workgroup per CU), and only when
-    // the slices taken off each tile's serial loop pay for the split: about
-    // 9.5 us for the partial sums and the summing pass against 0.46 us per
-    // 64-column slice of a lone workgroup (measured at batch 1 over the
-    // ResNet-50 and AlexNet layers), i.e. min_sl * (ks - 1) / ks > 20
+    int64_t base = 0;
+    int filters;
+    if (nd > 0) base += direct_tiles(Md, nd, p.NPQ, &filters);
+    if (ng > 0) base += direct_tiles(Mg, ng, p.NPQ, &filters);
     const int64_t cus = device_cus();
     if (base >= cus) return;
-    const int64_t ks = std::min<int64_t>(8, cus / base);
-    if (ks < 2 || (int64_t)min_sl * (ks - 1) <= 20 * ks) return;
-    p.ksplit = (int)ks;
+    const int most = (int)std::min<int64_t>(8, cus / base);
+    // at least 20 slices taken off each tile's serial loop
+    if (most < 2 || (int64_t)min_sl * (most - 1) <= 20 * most) return;
+    p.ksplit = most;
+    if (ng == 0) {
+        // The split that the time model expects to be fastest, the second
+        // pass and its launch at 5 us plus the partial sums written and read
+        // at 0.9 TB/s (fitted on layers of 192 to 12,544 pixels: [44, 696, 3, 3]
+        // on 8x8, batch 3: 24.8 us whole, 10.0 in 8 chunks; ResNet-50's last
+        // 3x3 at batch 8: 15.5 whole, 13.3 in 4, 17.4 in 8; at batch 64 16.5
+        // whole, 25.9 in 2).
+        float best = tile_time(a, tile_pick(a), 1);
+        p.ksplit = 1;
+        for (int ks = 2; ks <= most; ++ks) {
+            const float sum = 5.0f + (float)ks * (float)p.NPQ * (float)p.Cy * (8e-6f / 0.9f);
+            const float t = tile_time(a, kTileSplit, ks) + sum;
+            if (t < best) best = t, p.ksplit = ks;
+        }
+        if (p.ksplit == 1) return;
+    }
     p.part_stride = ((int64_t)p.NPQ * p.Cy + 3) / 4 * 4;
     p.part_off = (p.ws_need + 255) / 256 * 256;
     p.ws_need = p.part_off + ((size_t)p.ksplit * p.part_stride * 4 + 255) / 256 * 256;
@@ -1332,9 +1294,8 @@ void direct_plan(const sa_compact_sizes &s, ConvPlan *pl) {
         fine += (s.M[g] + 15) / 16 * 16;
     }
     if (n == 0) return;
-    int64_t blocks;
-    constexpr int kBN[2] = {128, 64};
-    const int BN = kBN[direct_pick(Ms, n, p.NPQ, &blocks)];
+    int BN;
+    direct_tiles(Ms, n, p.NPQ, &BN);
     int64_t coarse = 0;
     for (int i = 0; i < n; ++i) coarse += (int64_t)(Ms[i] + BN - 1) / BN * BN;
     p.direct_ig = maxM <= 64 && coarse * 100 >= fine * 115 && maxK >= 384 && maxK <= 512 && p.NPQ >= (1 << 16);
@@ -1551,7 +1512,7 @@ int conv_plan(const sa_conv_desc &d, ConvPlan *pl) {
             return fail(SA_E_UNSUPPORTED, "conv: gathered rows of group %d need 2 GiB or more", g);
         p.ws_need += ((size_t)bytes + 255) / 256 * 256;  // each gathered group has its own rows
     }
-    split_plan(p.eff, &p);
+    split_plan(d, p.eff, &p);
     direct_plan(p.eff, &p);
     return SA_OK;
 }
@@ -1648,12 +1609,13 @@ extern "C" int structadmm_conv_fwd(const sa_conv_desc *desc, hipStream_t stream)
     direct.NPQ = gathered.NPQ = pa.NPQ = NPQ;
     direct.H = d.H;
     direct.W = d.W;
+    direct.C = d.C;
     direct.D = d.D;
     direct.stride = d.stride;
     direct.pad = d.pad;
     direct.P = P;
     direct.Q = Q;
-    gathered.H = gathered.W = gathered.D = gathered.stride = gathered.P = gathered.Q = 1;
+    gathered.H = gathered.W = gathered.C = gathered.D = gathered.stride = gathered.P = gathered.Q = 1;
     gathered.pad = 0;
     pa.X = d.X;
     pa.x_bytes = x_bytes;
@@ -1714,6 +1676,7 @@ extern "C" int structadmm_conv_fwd(const sa_conv_desc *desc, hipStream_t stream)
         // the direct kernels see a stride-1, unpadded gC x gD CONV of the image
         direct.H = p.gH;
         direct.W = p.gW;
+        direct.C = p.gC;
         direct.D = p.gD;
         direct.stride = 1;
         direct.pad = 0;

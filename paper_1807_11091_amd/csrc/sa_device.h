@@ -76,9 +76,11 @@ __device__ inline uint32_t block_excl_scan(uint32_t x, uint32_t *tmp, uint32_t *
 
 // Exact floor(n / d) for 0 <= n < 2^31 and 1 <= d < 2^31 with a multiplier
 // m = ceil(2^(31+l) / d), l = ceil(log2 d) (Granlund & Montgomery, "Division
-// by invariant integers using multiplication", 1994, Theorem 4.2).
+// by invariant integers using multiplication", 1994, Theorem 4.2).  2^l <= 2d - 2
+// unless d is a power of two (m = 2^31), so m <= 2^32 - 2^32/d + 1 < 2^32 for
+// every d >= 3: a 32-bit multiplier, one 32 x 32 -> 64 bit multiply per division.
 struct FastDiv {
-    uint64_t mul;
+    uint32_t mul;
     uint32_t shift;  // 31 + l
     uint32_t d;
 };
@@ -88,7 +90,7 @@ inline FastDiv make_fastdiv(uint32_t d) {
     while ((uint64_t(1) << l) < d) ++l;
     FastDiv f;
     f.shift = 31 + l;
-    f.mul = ((uint64_t(1) << f.shift) + d - 1) / d;
+    f.mul = (uint32_t)(((uint64_t(1) << f.shift) + d - 1) / d);
     f.d = d;
     return f;
 }

@@ -1,0 +1,51 @@
+"""GPU parity of the direct CONV's tile shapes and fetch paths against the
+oracle (same bar as test_parity_conv: max|dY| / RMS(Y_ref) <= 2e-2, the bf16
+rounding of the output): edges of the 64- and 128-pixel tiles and of the 48-,
+64-, 80-, 128- and 160-filter ones, one to many slices of 64 columns, runs of
+channels that are and are not whole slices, more taps than the in-image bit
+mask holds, padding wider than the kernel, several conv groups, several tiles
+per workgroup, and columns split over workgroups."""
+import pytest
+
+import paper_1807_11091_amd as sa
+from test_parity_conv import conv_case
+
+pytestmark = pytest.mark.gpu
+
+D = {"path": {sa.CONV_DIRECT}}
+
+CASES = [
+    # N, Cin, H, W, A, C, D, stride, pad, groups, kind, keep
+    ((1, 64, 1, 1, 1, 1, 1, 1, 0, 1, sa.FILTER, 1.0), D),        # one output, one slice
+    ((1, 128, 9, 7, 65, 1, 1, 1, 0, 1, sa.FILTER, 1.0), D),      # 63 pixels, 65 filters, two slices
+    ((1, 192, 13, 5, 63, 1, 1, 1, 0, 1, sa.FILTER, 1.0), D),     # 65 pixels, three slices
+    ((3, 64, 9, 9, 33, 3, 3, 1, 1, 1, sa.FILTER, 1.0), D),       # a slice per tap
+    ((3, 64, 8, 10, 17, 3, 3, 1, 3, 1, sa.FILTER, 1.0), D),      # padding wider than the kernel
+    ((2, 64, 5, 1, 20, 3, 3, 1, 1, 1, sa.FILTER, 1.0), D),       # one pixel wide
+    ((2, 128, 15, 13, 70, 3, 3, 2, 1, 2, sa.FILTER, 0.7), D),    # two groups of 64 channels, stride 2
+    ((2, 64, 11, 12, 40, 5, 5, 2, 2, 1, sa.FILTER, 1.0), D),     # 25 taps, stride 2
+    ((2, 8, 15, 16, 24, 7, 7, 1, 3, 1, sa.FILTER, 1.0), D),      # 49 taps of 8 channels
+    ((30, 64, 9, 9, 90, 7, 5, 1, 2, 1, sa.FILTER, 1.0), D),       # 35 taps of 64 channels
+    ((2, 72, 9, 11, 51, 3, 3, 1, 1, 3, sa.FILTER, 0.7), D),      # runs of 24 channels, three groups
+    ((2, 96, 9, 11, 50, 3, 3, 2, 1, 1, sa.FILTER, 0.7), D),      # runs of 96: slices across taps
+    ((20, 64, 28, 28, 154, 3, 3, 1, 1, 1, sa.FILTER, 1.0), D),   # 154 filters: 160-filter tiles
+    ((40, 64, 31, 29, 130, 1, 1, 1, 0, 1, sa.FILTER, 1.0), D),   # many tiles of one slice
+    ((30, 64, 56, 56, 38, 1, 1, 1, 0, 1, sa.FILTER, 1.0), D),    # 38 filters: 48-filter tiles
+    ((48, 64, 28, 29, 77, 3, 3, 1, 1, 1, sa.FILTER, 1.0), D),    # 77 filters: 80-filter tiles
+    ((24, 128, 28, 28, 128, 3, 3, 1, 1, 1, sa.FILTER, 1.0), D),  # 128-filter tiles
+    ((9, 64, 20, 21, 200, 1, 1, 2, 0, 1, sa.FILTER, 1.0), D),    # 1x1 of stride 2
+    ((16, 256, 56, 56, 20, 1, 1, 1, 0, 1, sa.FILTER, 1.0), D),   # 20 filters, four slices
+    ((20, 64, 32, 32, 77, 1, 1, 1, 0, 1, sa.FILTER, 1.0), D),    # 77 filters, one slice
+    ((32, 24, 56, 56, 77, 1, 1, 1, 0, 1, sa.FILTER, 1.0), D),    # runs of 24 and 72 channels over the same shapes
+    ((16, 24, 28, 28, 154, 1, 1, 1, 0, 1, sa.FILTER, 1.0), D),
+    ((15, 72, 32, 32, 300, 1, 1, 1, 0, 1, sa.FILTER, 1.0), D),
+    ((25, 72, 28, 28, 100, 3, 3, 1, 1, 1, sa.FILTER, 1.0), D),
+    ((4, 512, 7, 7, 77, 3, 3, 1, 1, 1, sa.FILTER, 1.0), D),   # 72 slices
+    ((1, 512, 7, 7, 33, 3, 3, 1, 1, 1, sa.FILTER, 1.0), {"path": {sa.CONV_DIRECT}, "ksplit": 8}),
+    ((1, 704, 9, 8, 50, 3, 3, 1, 1, 2, sa.FILTER, 0.6), {"path": {sa.CONV_DIRECT}, "ksplit": 8}),  # runs of 352, split
+]
+
+
+@pytest.mark.parametrize("case,expect", CASES, ids=["x".join(str(v) for v in c[:10]) for c, _ in CASES])
+def test_conv_direct_tiles(case, expect):
+    conv_case(*case, seed=sum(case[:9]) + 5, dense_too=False, expect=expect)
