@@ -4,15 +4,15 @@
 // retraining (k_sgd).
 //
 // Data flow of structadmm_project for one dependency level of layers:
-//   k_expand_allowed  (channel, shape and element-wise layers with an input-channel
-//                     support) per-column support bytes; filter sets read the mask
+//   k_expand_allowed  (channel and shape layers with an input-channel support)
+//                     per-column support bytes; the other sets read the mask
 //   k_row_scores      filter sets: one wavefront per weight row, O_a in binary64
 //   k_col_partials    channel / shape sets: binary64 column sums per band of rows
 //   k_select          one workgroup per structured layer: final scores, radix
 //                     select of the k-th largest score bits in LDS, lowest-index
 //                     tie-break, mask + ascending kept_idx, per-column keep bytes
 //   k_elem_*          non-structured sets: 3 histogram passes over |v| bits, then an
-//                     order-preserving count / scan / apply
+//                     order-preserving count / apply
 //   k_apply           flat streaming Z (+ fused U', G) writer over every layer
 // Every reduction has a fixed order; no floating-point atomics are used.
 #include <hip/hip_runtime.h>
@@ -38,10 +38,13 @@ constexpr int kColThreads = 256;
 constexpr int kColBand = 32;       // rows per band of column partial sums
 constexpr int kColSlices = 4;      // row slices of a band (one wavefront each)
 constexpr int kSelThreads = 1024;
-constexpr int kElemThreads = 256;
+constexpr int kElemThreads = 256;  // count and apply passes
+constexpr int kHistThreads = 1024;
 constexpr int kElemPerThread = 8;
-constexpr int kElemChunk = kElemThreads * kElemPerThread;  // elements per workgroup
-constexpr int kElemHistBlocks = 1024;
+constexpr int kElemChunk = kElemThreads * kElemPerThread;  // entries per step of a workgroup
+constexpr int kHistChunk = kHistThreads * kElemPerThread;
+constexpr int kElemMaxBlocks = 1024;  // blocks per layer: a block adds up the counts of those before it
+constexpr int kElemTab = 32;          // element-wise layers per launch
 
 // ---------------------------------------------------------------- tables
 struct RowLayer {
@@ -509,10 +512,6 @@ struct ApplyTab {
     int32_t nl;
 };
 
-static_assert(sizeof(RowTab) < 8192 && sizeof(ColTab) < 8192 && sizeof(SelTab) < 8192 &&
-                  sizeof(DualTab) < 8192 && sizeof(ApplyTab) < 8192 && sizeof(SgdTab) < 8192,
-              "layer tables must fit the kernel-argument segment");
-
 constexpr int kApplyThreads = 256;
 constexpr int kApplyVec = 4;  // float4 per thread
 constexpr int kApplyChunk = kApplyThreads * kApplyVec * 4;
@@ -590,47 +589,59 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply(ApplyTab tab) {
 }
 
 // ---------------------------------------------------------------- element-wise
+// Every element-wise layer of a dependency level goes through one launch per
+// phase: zeroed histograms, three digit histograms of |v|, the counts, the
+// apply pass.  Small layers are launch latency: with a launch of its own per
+// layer and phase and a one-wavefront kernel between the passes AlexNet's five
+// layers (2.3 M weights) took 50 launches and 240 us; now 6 launches and 44 us.
 struct ElemState {
     uint32_t prefix;  // digits of T found so far; after the last pass, T itself
     uint32_t kk;      // rank of T among keys matching the prefix
-    uint32_t gt;      // keys known to exceed T
-    uint32_t pad;
 };
 
-struct ElemArgs {
+struct ElemLayer {
     const float *W;
     float *U;
     float *Z;
     float *G;
     uint8_t *mask;
     int32_t *kept_idx;
-    double *scores;          // [n] keys as |v| in binary64, or null
-    const uint8_t *allowed;  // [groups*K] or null
-    uint32_t *hist;          // [3][2048]
-    ElemState *state;
-    uint32_t *chunk_counts;  // [nchunks][2]: (gt, eq)
-    uint32_t *chunk_prefix;  // [nchunks][2]: exclusive prefixes
-    FastDiv divK;            // e -> row
-    int32_t n, K, Ag, k, nchunks, vec;
+    double *scores;         // [n] keys as |v| in binary64, or null
+    const uint8_t *inmask;  // [groups*B] input-channel support, or null
+    uint32_t *hist;         // [3][2048]
+    ElemState *state;       // [3]: after the first, second and third digit
+    uint2 *counts;          // keys above T and equal to T of each block's range
+    FastDiv divK, divAg, divCD;
+    int32_t n, K, B, k;
+    int32_t sub, hsub;  // chunks of kElemChunk entries per block, of kHistChunk per histogram block
     float rho;
 };
+struct ElemTab {
+    ElemLayer L[kElemTab];
+    int32_t begin[kElemTab + 1];   // first block of each layer
+    int32_t hbegin[kElemTab + 1];  // and of the histogram passes
+    int32_t nl;
+};
+
+static_assert(sizeof(RowTab) < 8192 && sizeof(ColTab) < 8192 && sizeof(SelTab) < 8192 &&
+                  sizeof(DualTab) < 8192 && sizeof(ApplyTab) < 8192 && sizeof(SgdTab) < 8192 && sizeof(ElemTab) < 8192,
+              "layer tables must fit the kernel-argument segment");
 
 // Is entry e inside the input-channel support?
-__device__ inline bool elem_allowed(uint32_t e, const ElemArgs &a) {
-    if (!a.allowed) return true;
-    uint32_t row = fdiv(e, a.divK);
-    uint32_t j = e - row * (uint32_t)a.K;
-    return a.allowed[(int64_t)(row / a.Ag) * a.K + j] != 0;
+__device__ inline bool elem_allowed(uint32_t e, const ElemLayer &a) {
+    if (!a.inmask) return true;
+    const uint32_t row = fdiv(e, a.divK);
+    return a.inmask[fdiv(row, a.divAg) * (uint32_t)a.B + fdiv(e - row * (uint32_t)a.K, a.divCD)] != 0;
 }
 
 // Key of entry e: |v| as binary32 bits (sign cleared); 0 outside the support.
-__device__ inline uint32_t elem_key(float v, uint32_t e, const ElemArgs &a) {
-    uint32_t key = __float_as_uint(v) & 0x7fffffffu;
+__device__ inline uint32_t elem_key(float v, uint32_t e, const ElemLayer &a) {
+    const uint32_t key = __float_as_uint(v) & 0x7fffffffu;
     return elem_allowed(e, a) ? key : 0u;
 }
 
-__device__ inline void elem_load8(const ElemArgs &a, int64_t e0, float *w, float *v) {
-    if (a.vec && e0 + 8 <= a.n) {
+__device__ inline void elem_load8(const ElemLayer &a, int64_t e0, float *w, float *v) {
+    if (e0 + 8 <= a.n) {  // e0 is a multiple of 8, W and U are 16-byte aligned
         float4 w0 = *reinterpret_cast<const float4 *>(a.W + e0);
         float4 w1 = *reinterpret_cast<const float4 *>(a.W + e0 + 4);
         float4 u0 = *reinterpret_cast<const float4 *>(a.U + e0);
@@ -654,90 +665,109 @@ __device__ inline void elem_load8(const ElemArgs &a, int64_t e0, float *w, float
     }
 }
 
-__global__ void k_elem_init(ElemArgs a) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < 3 * 2048) a.hist[i] = 0;
-    if (i == 0) {
-        a.state->prefix = a.k > 0 ? 0u : 0x80000000u;  // k = 0: T above every key
-        a.state->kk = (uint32_t)a.k;
-        a.state->gt = 0;
-        a.state->pad = 0;
+__global__ __launch_bounds__(kHistThreads) void k_elem_init(ElemTab tab) {
+    uint32_t *h = tab.L[blockIdx.x].hist;
+    for (int i = threadIdx.x; i < 3 * 2048; i += kHistThreads) h[i] = 0;
+}
+
+// The digit of pass `pass` that holds the kk-th largest key, and the rank
+// within it: every workgroup works it out for itself from the finished
+// histogram (2048 or 512 bins, a few per thread), which spares a launch
+// between the passes.  `tmp` and `out`: LDS of the workgroup.
+template <int kThreads, int kBits>
+__device__ inline ElemState elem_find(const ElemLayer &a, int pass, ElemState s, uint32_t *tmp, ElemState *out) {
+    constexpr int kPer = (1 << kBits) / kThreads;
+    const int top = (1 << kBits) - 1 - (int)threadIdx.x * kPer;  // descending
+    const uint32_t *gh = a.hist + pass * 2048 + top;
+    uint32_t c[kPer], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) sum += (c[q] = gh[-q]);
+    uint32_t total;
+    uint32_t above = block_excl_scan(sum, tmp, &total);
+    if (above < s.kk && s.kk <= above + sum) {  // exactly one thread
+        int q = 0;
+#pragma unroll
+        for (int i = 0; i + 1 < kPer; ++i)
+            if (q == i && above + c[i] < s.kk) {
+                above += c[i];
+                q = i + 1;
+            }
+        *out = ElemState{(s.prefix << kBits) | (uint32_t)(top - q), s.kk - above};
     }
+    __syncthreads();
+    return *out;
 }
 
 // Histogram of one digit of the keys that match the digits found so far.
 // Digits: pass 0 = bits 30..20, pass 1 = bits 19..9, pass 2 = bits 8..0.
-__global__ __launch_bounds__(kElemThreads) void k_elem_hist(ElemArgs a, int pass) {
+// Adding the workgroups' histograms up in memory bounds the pass (the reads
+// alone take 3 us of AlexNet's 2.3 M weights), so a workgroup is large: 7.9,
+// 9.2 and 6.9 us with 1024 threads, 8.4, 12 and 7.4 with 512, 11.9, 14 and 9.8
+// with 256.
+__global__ __launch_bounds__(kHistThreads) void k_elem_hist(ElemTab tab, int pass) {
     __shared__ uint32_t h[2048];
-    for (int i = threadIdx.x; i < 2048; i += kElemThreads) h[i] = 0;
-    __syncthreads();
-    const uint32_t prefix = a.state->prefix;
+    __shared__ uint32_t tmp[kHistThreads / kWave + 1];
+    __shared__ ElemState found;
+    const int li = find_layer(tab.hbegin, tab.nl, blockIdx.x);
+    const ElemLayer &a = tab.L[li];
+    if (a.k == 0) return;
+    const int blk = blockIdx.x - tab.hbegin[li];
+    for (int i = threadIdx.x; i < 2048; i += kHistThreads) h[i] = 0;
+    const int64_t first = (int64_t)blk * a.hsub * kHistChunk + (int64_t)threadIdx.x * kElemPerThread;
+    float w[8], v[8];
+    elem_load8(a, first, w, v);  // in flight while the digit of the pass before is found
+    ElemState s{0u, (uint32_t)a.k};
+    if (pass > 0) {
+        if (pass > 1) s = a.state[pass - 2];
+        s = elem_find<kHistThreads, 11>(a, pass - 1, s, tmp, &found);
+        if (blk == 0 && threadIdx.x == 0) a.state[pass - 1] = s;
+    } else {
+        __syncthreads();
+    }
     const int dshift = pass == 0 ? 20 : (pass == 1 ? 9 : 0);
     const uint32_t dmask = pass == 2 ? 0x1ffu : 0x7ffu;
     const int mshift = pass == 0 ? 31 : (pass == 1 ? 20 : 9);
-    for (int c = blockIdx.x; c < a.nchunks; c += gridDim.x) {
-        const int64_t e0 = (int64_t)c * kElemChunk + (int64_t)threadIdx.x * kElemPerThread;
-        float w[8], v[8];
-        elem_load8(a, e0, w, v);
+    for (int c = 0; c < a.hsub; ++c) {
+        const int64_t e0 = first + (int64_t)c * kHistChunk;
+        if (c > 0) elem_load8(a, e0, w, v);
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             if (e0 + q >= a.n) break;
-            uint32_t key = elem_key(v[q], (uint32_t)(e0 + q), a);
-            if (pass == 0 || (key >> mshift) == prefix) atomicAdd(&h[(key >> dshift) & dmask], 1u);
+            const uint32_t key = elem_key(v[q], (uint32_t)(e0 + q), a);
+            if (pass == 0 || (key >> mshift) == s.prefix) atomicAdd(&h[(key >> dshift) & dmask], 1u);
         }
     }
     __syncthreads();
     uint32_t *gh = a.hist + pass * 2048;
-    for (int i = threadIdx.x; i < 2048; i += kElemThreads)
+    for (int i = threadIdx.x; i < 2048; i += kHistThreads)
         if (h[i]) atomicAdd(&gh[i], h[i]);
 }
 
-// Picks the digit holding the kk-th largest key (one wavefront).
-__global__ void k_elem_find(ElemArgs a, int pass) {
-    const int lane = threadIdx.x;
-    const int bins = pass == 2 ? 512 : 2048;
-    const int bits = pass == 2 ? 9 : 11;
-    const int per = bins / kWave;
-    const uint32_t *gh = a.hist + pass * 2048;
-    const uint32_t kk = a.state->kk;
-    const uint32_t prefix = a.state->prefix;
-    uint32_t sum = 0;
-    for (int q = 0; q < per; ++q) sum += gh[bins - 1 - lane * per - q];
-    uint32_t incl = wave_incl_scan(sum);
-    uint32_t excl = incl - sum;
-    if (excl < kk && kk <= incl) {
-        uint32_t above = excl;
-        int d = 0;
-        for (int q = 0; q < per; ++q) {
-            int dig = bins - 1 - lane * per - q;
-            uint32_t c = gh[dig];
-            if (above + c >= kk) {
-                d = dig;
-                break;
-            }
-            above += c;
-        }
-        a.state->prefix = (prefix << bits) | (uint32_t)d;
-        a.state->kk = kk - above;
-        a.state->gt += above;
-    }
-}
-
-// Per-chunk counts of keys above T and equal to T.
-__global__ __launch_bounds__(kElemThreads) void k_elem_count(ElemArgs a) {
+// Per-block counts of keys above T and equal to T.
+__global__ __launch_bounds__(kElemThreads) void k_elem_count(ElemTab tab) {
     __shared__ uint32_t red[2][kElemThreads / kWave];
-    const int c = blockIdx.x;
-    const uint32_t T = a.state->prefix;
-    const int64_t e0 = (int64_t)c * kElemChunk + (int64_t)threadIdx.x * kElemPerThread;
+    __shared__ uint32_t tmp[kElemThreads / kWave + 1];
+    __shared__ ElemState found;
+    const int li = find_layer(tab.begin, tab.nl, blockIdx.x);
+    const ElemLayer &a = tab.L[li];
+    const int blk = blockIdx.x - tab.begin[li];
+    const int64_t first = (int64_t)blk * a.sub * kElemChunk + (int64_t)threadIdx.x * kElemPerThread;
     float w[8], v[8];
-    elem_load8(a, e0, w, v);
+    elem_load8(a, first, w, v);
+    ElemState s{0x80000000u, 0u};  // k = 0: T above every key
+    if (a.k > 0) s = elem_find<kElemThreads, 9>(a, 2, a.state[1], tmp, &found);
+    if (blk == 0 && threadIdx.x == 0) a.state[2] = s;
     uint32_t gt = 0, eq = 0;
+    for (int c = 0; c < a.sub; ++c) {
+        const int64_t e0 = first + (int64_t)c * kElemChunk;
+        if (c > 0) elem_load8(a, e0, w, v);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        if (e0 + q >= a.n) break;
-        uint32_t key = elem_key(v[q], (uint32_t)(e0 + q), a);
-        gt += key > T;
-        eq += key == T;
+        for (int q = 0; q < 8; ++q) {
+            if (e0 + q >= a.n) break;
+            const uint32_t key = elem_key(v[q], (uint32_t)(e0 + q), a);
+            gt += key > s.prefix;
+            eq += key == s.prefix;
+        }
     }
     gt = wave_sum_u32(gt);
     eq = wave_sum_u32(eq);
@@ -753,82 +783,110 @@ __global__ __launch_bounds__(kElemThreads) void k_elem_count(ElemArgs a) {
             g += red[0][i];
             e += red[1][i];
         }
-        a.chunk_counts[2 * c] = g;
-        a.chunk_counts[2 * c + 1] = e;
+        a.counts[blk] = make_uint2(g, e);
     }
 }
 
-// Exclusive prefixes of the per-chunk counts (one workgroup, chunk order).
-__global__ __launch_bounds__(1024) void k_elem_scan(ElemArgs a) {
-    __shared__ uint32_t tmp[1024 / kWave + 1];
-    uint32_t carry_gt = 0, carry_eq = 0;
-    for (int base = 0; base < a.nchunks; base += 1024) {
-        const int c = base + threadIdx.x;
-        uint32_t g = c < a.nchunks ? a.chunk_counts[2 * c] : 0u;
-        uint32_t e = c < a.nchunks ? a.chunk_counts[2 * c + 1] : 0u;
-        uint32_t tg, te;
-        uint32_t pg = block_excl_scan(g, tmp, &tg);
-        uint32_t pe = block_excl_scan(e, tmp, &te);
-        if (c < a.nchunks) {
-            a.chunk_prefix[2 * c] = carry_gt + pg;
-            a.chunk_prefix[2 * c + 1] = carry_eq + pe;
-        }
-        carry_gt += tg;
-        carry_eq += te;
-    }
-}
-
-// Mask, ascending kept_idx, Z (+ fused U', G) for the non-structured set.
-__global__ __launch_bounds__(kElemThreads) void k_elem_apply(ElemArgs a) {
+// Mask, ascending kept_idx, Z (+ fused U', G) for the non-structured set.  The
+// entries kept before a position are the keys above T before it and the first
+// `need` keys equal to T; each block adds up the counts of the blocks before it
+// (at most kElemMaxBlocks).  Bound by its 16 to 21 bytes an entry; workgroups of
+// 256 threads: 12.5 us of AlexNet's 2.3 M weights, 512 take 16.5 and 1024 18.5.
+__global__ __launch_bounds__(kElemThreads) void k_elem_apply(ElemTab tab) {
     __shared__ uint32_t tmp[kElemThreads / kWave + 1];
-    const int c = blockIdx.x;
-    const uint32_t T = a.state->prefix;
-    const uint32_t need = a.state->kk;  // ties at T kept overall (0 when k = 0)
-    const uint32_t gt_before = a.chunk_prefix[2 * c];
-    const uint32_t eq_before = a.chunk_prefix[2 * c + 1];
-    const int64_t e0 = (int64_t)c * kElemChunk + (int64_t)threadIdx.x * kElemPerThread;
+    __shared__ uint32_t red[2][kElemThreads / kWave];
+    const int li = find_layer(tab.begin, tab.nl, blockIdx.x);
+    const ElemLayer &a = tab.L[li];
+    const int blk = blockIdx.x - tab.begin[li];
+    const int wave = threadIdx.x >> 6;
+    const int64_t first = (int64_t)blk * a.sub * kElemChunk + (int64_t)threadIdx.x * kElemPerThread;
     float w[8], v[8];
-    elem_load8(a, e0, w, v);
-    uint32_t key[8];
-    uint32_t eq = 0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        key[q] = (e0 + q < a.n) ? elem_key(v[q], (uint32_t)(e0 + q), a) : 0u;
-        eq += (e0 + q < a.n) && key[q] == T;
+    elem_load8(a, first, w, v);
+    const uint32_t T = a.state[2].prefix;
+    const uint32_t need = a.state[2].kk;  // keys equal to T that are kept (0 when k = 0)
+    uint32_t gt_before = 0, eq_before = 0;
+    for (int c = threadIdx.x; c < blk; c += kElemThreads) {
+        const uint2 t = a.counts[c];
+        gt_before += t.x;
+        eq_before += t.y;
     }
-    uint32_t total;
-    uint32_t eq_rank = eq_before + block_excl_scan(eq, tmp, &total);
-    bool keep[8];
-    uint32_t kept = 0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        keep[q] = false;
-        if (e0 + q < a.n && a.k > 0) {
-            if (key[q] > T) keep[q] = true;
-            else if (key[q] == T) keep[q] = (eq_rank++ < need);
-        }
-        kept += keep[q];
+    gt_before = wave_sum_u32(gt_before);
+    eq_before = wave_sum_u32(eq_before);
+    if ((threadIdx.x & 63) == 0) {
+        red[0][wave] = gt_before;
+        red[1][wave] = eq_before;
     }
-    const uint32_t kept_chunk_before = gt_before + min(eq_before, need);
-    uint32_t pos = kept_chunk_before + block_excl_scan(kept, tmp, &total);
+    __syncthreads();
+    gt_before = eq_before = 0;
+    for (int i = 0; i < kElemThreads / kWave; ++i) {
+        gt_before += red[0][i];
+        eq_before += red[1][i];
+    }
     const bool fused = a.G != nullptr;
+    const bool mvec = ((uintptr_t)a.mask & 7) == 0;
+    for (int c = 0; c < a.sub; ++c) {
+        const int64_t e0 = first + (int64_t)c * kElemChunk;
+        if (c > 0) elem_load8(a, e0, w, v);
+        uint32_t key[8], cnt = 0;  // cnt: keys above T, and equal to T in the upper half
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int64_t e = e0 + q;
-        if (e >= a.n) break;
-        // a kept entry outside the support (score 0) still projects to 0
-        const float z = (keep[q] && elem_allowed((uint32_t)e, a)) ? v[q] : 0.0f;
-        a.Z[e] = z;
-        a.mask[e] = keep[q] ? 1 : 0;
-        if (a.scores) a.scores[e] = (double)__uint_as_float(key[q]);
-        if (keep[q] && pos < (uint32_t)a.k) a.kept_idx[pos] = (int32_t)e;
-        pos += keep[q] ? 1u : 0u;
-        if (fused) {
-            float un = v[q] - z;
-            float wz = w[q] - z;
-            float s = wz + un;
-            a.U[e] = un;
-            a.G[e] = a.rho * s;
+        for (int q = 0; q < 8; ++q) {
+            key[q] = (e0 + q < a.n) ? elem_key(v[q], (uint32_t)(e0 + q), a) : 0u;
+            if (e0 + q < a.n) cnt += key[q] > T ? 1u : (key[q] == T ? 0x10000u : 0u);
+        }
+        uint32_t total;  // at most kElemChunk of either kind: no carry between the halves
+        const uint32_t before = block_excl_scan(cnt, tmp, &total);
+        uint32_t eq_rank = eq_before + (before >> 16);
+        uint32_t pos = gt_before + (before & 0xffffu) + min(eq_rank, need);
+        gt_before += total & 0xffffu;
+        eq_before += total >> 16;
+        float z[8], un[8], g[8];
+        uint32_t bits = 0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int64_t e = e0 + q;
+            bool keep = false;
+            if (e < a.n && a.k > 0) keep = key[q] > T || (key[q] == T && eq_rank++ < need);
+            // a kept entry outside the support (score 0) still projects to 0
+            z[q] = (keep && elem_allowed((uint32_t)e, a)) ? v[q] : 0.0f;
+            un[q] = v[q] - z[q];
+            const float wz = w[q] - z[q];
+            const float sum = wz + un[q];
+            g[q] = a.rho * sum;
+            bits |= keep ? 1u << q : 0u;
+            if (keep && pos < (uint32_t)a.k) a.kept_idx[pos] = (int32_t)e;
+            pos += keep ? 1u : 0u;
+            if (a.scores && e < a.n) a.scores[e] = (double)__uint_as_float(key[q]);
+        }
+        if (e0 + 8 <= a.n) {
+            nt_store4(a.Z + e0, z);
+            nt_store4(a.Z + e0 + 4, z + 4);
+            if (fused) {
+                nt_store4(a.U + e0, un);
+                nt_store4(a.U + e0 + 4, un + 4);
+                nt_store4(a.G + e0, g);
+                nt_store4(a.G + e0 + 4, g + 4);
+            }
+            // bit q of a nibble to byte q
+            const uint32_t lo = ((bits & 15u) * 0x00204081u) & 0x01010101u;
+            const uint32_t hi = ((bits >> 4) * 0x00204081u) & 0x01010101u;
+            if (mvec) {
+                *reinterpret_cast<uint2 *>(a.mask + e0) = make_uint2(lo, hi);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) a.mask[e0 + q] = (uint8_t)((bits >> q) & 1u);
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int64_t e = e0 + q;
+                if (e >= a.n) break;
+                a.Z[e] = z[q];
+                a.mask[e] = (uint8_t)((bits >> q) & 1u);
+                if (fused) {
+                    a.U[e] = un[q];
+                    a.G[e] = g[q];
+                }
+            }
         }
     }
 }
@@ -959,7 +1017,7 @@ __global__ __launch_bounds__(kSgdThreads) void k_sgd(SgdTab tab) {
 // ---------------------------------------------------------------- host planning
 struct LayerPlan {
     int64_t G;
-    int K, CD, Ag, R, rchunks, ritems, nbands, ctiles, vec, nchunks;
+    int K, CD, Ag, R, rchunks, ritems, nbands, ctiles, vec, nblk, sub, hblk, hsub;
     size_t off_scores, off_rowpart, off_partials, off_allowed, off_colkeep, off_elem;
     size_t end;
 };
@@ -981,7 +1039,12 @@ void plan_layer(const sa_project_desc &d, size_t start, LayerPlan &p) {
     const int cols_per_block = (kColThreads / kColSlices) * (p.vec ? 4 : 1);
     p.ctiles = (p.K + cols_per_block - 1) / cols_per_block;
     const int64_t n = d.A * d.B * d.C * d.D;
-    p.nchunks = (int)((n + kElemChunk - 1) / kElemChunk);
+    const int64_t chunks = (n + kElemChunk - 1) / kElemChunk;
+    p.sub = (int)((chunks + kElemMaxBlocks - 1) / kElemMaxBlocks);
+    p.nblk = (int)((chunks + p.sub - 1) / p.sub);
+    const int64_t hchunks = (n + kHistChunk - 1) / kHistChunk;
+    p.hsub = (int)((hchunks + kElemMaxBlocks - 1) / kElemMaxBlocks);
+    p.hblk = (int)((hchunks + p.hsub - 1) / p.hsub);
     size_t off = align256(start);
     p.off_scores = p.off_rowpart = p.off_partials = p.off_allowed = p.off_colkeep = p.off_elem = SIZE_MAX;
     if (d.kind != SA_ELEMENT && !d.scores) {
@@ -1006,8 +1069,9 @@ void plan_layer(const sa_project_desc &d, size_t start, LayerPlan &p) {
     }
     if (d.kind == SA_ELEMENT) {
         p.off_elem = off;
-        off = align256(off + sizeof(uint32_t) * 3 * 2048 + sizeof(ElemState) +
-                       sizeof(uint32_t) * 4 * (size_t)p.nchunks + 256);
+        // 16 bytes per chunk: the counts need 8 per block; the size callers
+        // were told, and with it what the held scratch takes, stays the same
+        off = align256(off + sizeof(uint32_t) * 3 * 2048 + 16 + 256 + 16 * (size_t)chunks);
     }
     p.end = off;
 }
@@ -1128,6 +1192,26 @@ int project_impl(const sa_project_desc *layers, int n_layers, void *ws, size_t w
         max_level = std::max(max_level, level[i]);
     }
 
+    // May layer ids[m] share launches with layers ids[0..m)?  Layers of a level
+    // run in the order given where one writes what another reads or writes.
+    auto apart = [](const sa_project_desc *l, const int *ids, int m) {
+        auto meet = [](const sa_project_desc &a, const float *p, const sa_project_desc &b, const float *q) {
+            const int64_t na = a.A * a.B * a.C * a.D, nb = b.A * b.B * b.C * b.D;
+            return p && q && (uintptr_t)p < (uintptr_t)(q + nb) && (uintptr_t)q < (uintptr_t)(p + na);
+        };
+        const sa_project_desc &b = l[ids[m]];
+        for (int j = 0; j < m; ++j) {
+            const sa_project_desc &a = l[ids[j]];
+            for (const float *w : {(const float *)a.Z, (const float *)a.G, (const float *)(a.G ? a.U : nullptr)})
+                for (const float *t : {b.W, (const float *)b.U, (const float *)b.Z, (const float *)b.G})
+                    if (meet(a, w, b, t)) return false;
+            for (const float *w : {(const float *)b.Z, (const float *)b.G, (const float *)(b.G ? b.U : nullptr)})
+                for (const float *t : {a.W, (const float *)a.U})
+                    if (meet(b, w, a, t)) return false;
+        }
+        return true;
+    };
+
     auto fill_row = [&](int i, RowLayer &R) {
         const sa_project_desc &d = layers[i];
         const LayerPlan &p = plan[i];
@@ -1155,11 +1239,11 @@ int project_impl(const sa_project_desc *layers, int n_layers, void *ws, size_t w
         for (int i = 0; i < n_layers; ++i)
             if (level[i] == lv) ids.push_back(i);
 
-        // allowed bytes for layers with a channel support (filter sets read
-        // the mask itself)
+        // allowed bytes for layers with a channel support (filter and
+        // element-wise sets read the mask itself)
         for (int i : ids) {
             const sa_project_desc &d = layers[i];
-            if (!d.in_ch_mask || d.kind == SA_FILTER) continue;
+            if (!d.in_ch_mask || d.kind == SA_FILTER || d.kind == SA_ELEMENT) continue;
             const LayerPlan &p = plan[i];
             int64_t total = (int64_t)d.groups * p.K;
             int blocks = (int)std::min<int64_t>(1024, (total + 255) / 256);
@@ -1256,50 +1340,65 @@ int project_impl(const sa_project_desc *layers, int n_layers, void *ws, size_t w
             }
         }
         // element-wise layers
-        for (int i : ids) {
-            const sa_project_desc &d = layers[i];
-            if (d.kind != SA_ELEMENT) continue;
-            const LayerPlan &p = plan[i];
-            ElemArgs a;
-            memset(&a, 0, sizeof a);
-            a.W = d.W;
-            a.U = d.U;
-            a.Z = d.Z;
-            a.G = d.G;
-            a.mask = d.mask;
-            a.kept_idx = d.kept_idx;
-            a.scores = d.scores;
-            a.allowed = d.in_ch_mask ? ws_at<uint8_t>(ws, p.off_allowed) : nullptr;
-            char *eb = ws_at<char>(ws, p.off_elem);
-            a.hist = reinterpret_cast<uint32_t *>(eb);
-            a.state = reinterpret_cast<ElemState *>(eb + sizeof(uint32_t) * 3 * 2048);
-            a.chunk_counts = reinterpret_cast<uint32_t *>(eb + sizeof(uint32_t) * 3 * 2048 + 256);
-            a.chunk_prefix = a.chunk_counts + 2 * (size_t)p.nchunks;
-            a.divK = make_fastdiv((uint32_t)p.K);
-            a.n = (int32_t)(d.A * d.B * d.C * d.D);
-            a.K = p.K;
-            a.Ag = p.Ag;
-            a.k = (int32_t)d.k;
-            a.nchunks = p.nchunks;
-            a.vec = 1;  // n is a multiple of 4 only sometimes; elem_load8 checks the tail
-            a.rho = d.rho;
-            hipLaunchKernelGGL(k_elem_init, dim3((3 * 2048 + 255) / 256), dim3(256), 0, stream, a);
-            if (int rc = launch_check("k_elem_init")) return rc;
-            if (d.k > 0) {
-                const int hb = std::min(p.nchunks, kElemHistBlocks);
-                for (int pass = 0; pass < 3; ++pass) {
-                    hipLaunchKernelGGL(k_elem_hist, dim3(hb), dim3(kElemThreads), 0, stream, a, pass);
-                    if (int rc = launch_check("k_elem_hist")) return rc;
-                    hipLaunchKernelGGL(k_elem_find, dim3(1), dim3(kWave), 0, stream, a, pass);
-                    if (int rc = launch_check("k_elem_find")) return rc;
+        {
+            std::vector<int> el;
+            for (int i : ids)
+                if (layers[i].kind == SA_ELEMENT) el.push_back(i);
+            for (size_t s = 0, step = 0; s < el.size(); s += step) {
+                ElemTab tab;
+                memset(&tab, 0, sizeof tab);
+                step = 1;
+                while (step < (size_t)kElemTab && s + step < el.size() && apart(layers, &el[s], (int)step)) ++step;
+                tab.nl = (int)step;
+                int blocks = 0, hblocks = 0;
+                bool any = false;
+                for (int t = 0; t < tab.nl; ++t) {
+                    const sa_project_desc &d = layers[el[s + t]];
+                    const LayerPlan &p = plan[el[s + t]];
+                    ElemLayer &a = tab.L[t];
+                    a.W = d.W;
+                    a.U = d.U;
+                    a.Z = d.Z;
+                    a.G = d.G;
+                    a.mask = d.mask;
+                    a.kept_idx = d.kept_idx;
+                    a.scores = d.scores;
+                    a.inmask = d.in_ch_mask;
+                    char *eb = ws_at<char>(ws, p.off_elem);
+                    a.hist = reinterpret_cast<uint32_t *>(eb);
+                    a.state = reinterpret_cast<ElemState *>(eb + sizeof(uint32_t) * 3 * 2048);
+                    a.counts = reinterpret_cast<uint2 *>(eb + sizeof(uint32_t) * 3 * 2048 + 256);
+                    a.divK = make_fastdiv((uint32_t)p.K);
+                    a.divAg = make_fastdiv((uint32_t)p.Ag);
+                    a.divCD = make_fastdiv((uint32_t)p.CD);
+                    a.n = (int32_t)(d.A * d.B * d.C * d.D);
+                    a.K = p.K;
+                    a.B = (int)d.B;
+                    a.k = (int32_t)d.k;
+                    a.sub = p.sub;
+                    a.hsub = p.hsub;
+                    a.rho = d.rho;
+                    any = any || d.k > 0;
+                    tab.begin[t] = blocks;
+                    blocks += p.nblk;
+                    tab.hbegin[t] = hblocks;
+                    hblocks += p.hblk;
                 }
+                tab.begin[tab.nl] = blocks;
+                tab.hbegin[tab.nl] = hblocks;
+                if (any) {
+                    hipLaunchKernelGGL(k_elem_init, dim3(tab.nl), dim3(kHistThreads), 0, stream, tab);
+                    if (int rc = launch_check("k_elem_init")) return rc;
+                    for (int pass = 0; pass < 3; ++pass) {
+                        hipLaunchKernelGGL(k_elem_hist, dim3(hblocks), dim3(kHistThreads), 0, stream, tab, pass);
+                        if (int rc = launch_check("k_elem_hist")) return rc;
+                    }
+                }
+                hipLaunchKernelGGL(k_elem_count, dim3(blocks), dim3(kElemThreads), 0, stream, tab);
+                if (int rc = launch_check("k_elem_count")) return rc;
+                hipLaunchKernelGGL(k_elem_apply, dim3(blocks), dim3(kElemThreads), 0, stream, tab);
+                if (int rc = launch_check("k_elem_apply")) return rc;
             }
-            hipLaunchKernelGGL(k_elem_count, dim3(p.nchunks), dim3(kElemThreads), 0, stream, a);
-            if (int rc = launch_check("k_elem_count")) return rc;
-            hipLaunchKernelGGL(k_elem_scan, dim3(1), dim3(1024), 0, stream, a);
-            if (int rc = launch_check("k_elem_scan")) return rc;
-            hipLaunchKernelGGL(k_elem_apply, dim3(p.nchunks), dim3(kElemThreads), 0, stream, a);
-            if (int rc = launch_check("k_elem_apply")) return rc;
         }
     }
     // apply for every structured layer, all levels at once: a level only needs

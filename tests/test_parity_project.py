@@ -13,7 +13,7 @@ import pytest
 
 import oracle
 import paper_1807_11091_amd as sa
-from gpu_helpers import (GpuLayer, bitwise_equal, boundary_gap, n_groups, rel_l2, run_project,
+from gpu_helpers import (DEV, GpuLayer, bitwise_equal, boundary_gap, n_groups, rel_l2, run_project,
                          to_dev, torch)
 from workloads import WORKLOADS, layer_tensors
 
@@ -238,3 +238,56 @@ def test_project_is_deterministic_across_streams():
     for a, b in zip(*outs):
         for key in a:
             assert bitwise_equal(a[key], b[key]), key
+
+
+def element_case(shape, groups, rng, values="random"):
+    W = (0.05 * rng.standard_normal(shape)).astype(np.float32)
+    U = (0.01 * rng.standard_normal(shape)).astype(np.float32)
+    if values == "ties":  # few distinct magnitudes: long runs of equal keys across workgroups
+        W, U = (rng.integers(-2, 3, size=shape) * 0.5).astype(np.float32), np.zeros(shape, np.float32)
+    elif values == "wide":  # every exponent, infinities and zeros of both signs
+        W = (rng.standard_normal(shape) * 2.0 ** rng.integers(-140, 120, size=shape)).astype(np.float32)
+        W.reshape(-1)[:: 97] = np.inf
+        W.reshape(-1)[5:: 89] = -0.0
+        U = np.zeros(shape, np.float32)
+    return W, U
+
+
+@pytest.mark.parametrize("values", ["random", "ties", "wide"])
+def test_project_element_layers_share_launches(values):
+    """Element-wise layers of one level: sizes at the edges of a workgroup's
+    range (2048 entries, 8192 in the histograms), beyond 1024 workgroups (several
+    chunks each), k = 0 beside k > 0, a support, and more layers than a table holds."""
+    rng = np.random.default_rng(41)
+    specs = [((1, 1, 1, 1), 1), ((2, 1024, 1, 1), 1), ((3, 683, 1, 1), 1), ((8, 1024, 1, 1), 2), ((1, 8193, 1, 1), 1),
+             ((6, 341, 2, 1), 3), ((1500, 1401, 1, 1), 1)] + [((4 + i, 5, 3, 3), 1) for i in range(30)]
+    layers, refs, ks = [], [], []
+    for i, (shape, groups) in enumerate(specs):
+        W, U = element_case(shape, groups, rng, values)
+        k = [0, W.size, W.size // 3, 1, W.size - 1][(i + 2) % 5]
+        m = (rng.random(groups * shape[1]) < 0.6).astype(np.uint8) if i % 3 == 1 else None
+        fused = values != "wide" and i % 2 == 0  # inf - inf has no value to compare
+        refs.append(oracle_ref(W, U, sa.ELEMENT, k, groups, in_ch_mask=m, rho=1e-3, fused=fused))
+        layers.append(GpuLayer(W, U, sa.ELEMENT, k, groups, in_ch_mask=m, rho=1e-3, fused=fused))
+        ks.append((k, fused))
+    for i, (g, r) in enumerate(zip(run_project(layers), refs)):
+        assert np.array_equal(g.pop("scores"), r["scores"]), f"{values} layer {i} scores"  # |v| itself
+        check(g, r, sa.ELEMENT, *ks[i], f"{values} layer {i}")
+
+
+def test_project_element_mask_off_alignment_and_chained_buffers():
+    """A mask at an odd address; a layer that reads what an earlier one of the call writes."""
+    t, rng = torch(), np.random.default_rng(43)
+    W, U = element_case((16, 33, 3, 3), 1, rng)
+    k1, k2 = W.size // 2, W.size // 4
+    first, second = (GpuLayer(W, U, sa.ELEMENT, k, rho=1e-3, fused=True) for k in (k1, k2))
+    first.mask = t.full((W.size + 1,), 7, dtype=t.uint8, device=DEV)[1:]
+    first.layer = sa.ProjectLayer(first.W, first.U, first.Z, first.mask, first.kept, sa.ELEMENT, k1, 1, None,
+                                  first.scores, 1e-3, first.G)
+    second.layer = sa.ProjectLayer(first.Z, second.U, second.Z, second.mask, second.kept, sa.ELEMENT, k2, 1, None,
+                                   second.scores, 1e-3, second.G)
+    r1 = oracle_ref(W, U, sa.ELEMENT, k1, rho=1e-3, fused=True)
+    r2 = oracle_ref(r1["Z"], U, sa.ELEMENT, k2, rho=1e-3, fused=True)
+    got = run_project([first, second])
+    check(got[0], r1, sa.ELEMENT, k1, True, "first")
+    check(got[1], r2, sa.ELEMENT, k2, True, "second")
