@@ -393,9 +393,10 @@ int structadmm_csr(const sa_csr_desc *desc, hipStream_t stream);
  *     val[e] * X[n, p*stride - pad + c, q*stride - pad + d, gc*B + b]
  * with conv group gc = a / (A / groups) and col[e] = (b*C + c)*D + d; zero
  * outside the image (cross-correlation, no bias, no dilation).  bfloat16
- * operands, binary32 accumulation (packed bf16 dot products on the vector
- * ALUs: a pattern of single weights has no dense tile for the matrix cores),
- * bfloat16 output (nearest even).  The result equals structadmm_conv_fwd over
+ * operands, binary32 accumulation (packed bf16 dot products on the vector ALUs,
+ * or from some density up the matrix cores over the scratch's dense copy, which
+ * is only used where the scratch has the bytes asked for), bfloat16 output
+ * (nearest even).  The result equals structadmm_conv_fwd over
  * the uncompacted matrix of the same weights up to the order of the sums.
  * X: bfloat16 NHWC [N, H, W, Cx], Cx = groups*B a multiple of 8, 16-byte
  *    aligned, smaller than 2 GiB.
@@ -416,7 +417,8 @@ typedef struct sa_sparse_conv_desc {
     uint16_t *Y;
     void *ws;                  /* device scratch of structadmm_conv_sparse_workspace()
                                   bytes, 256-byte aligned: the entries' LDS offsets
-                                  and values with every row padded to 8 entries */
+                                  and values with every row padded to 8 entries,
+                                  and the dense matrix where that is faster */
     size_t ws_bytes;
     int32_t reuse_ws;          /* 0: (re)build the padded entries in ws, then run
                                   the CONV.  Nonzero: ws already holds what an
