@@ -1251,7 +1251,7 @@ void split_plan(const sa_conv_desc &d, const sa_compact_sizes &s, ConvPlan *pl) 
     p.ksplit = most;
     if (ng == 0) {
         // The split that the time model expects to be fastest, the second
-        // pass and its launch at 5 us plus the partial sums written and read
+        // pass and its launch at 4 us plus the partial sums written and read
         // at 0.9 TB/s (fitted on layers of 192 to 12,544 pixels: [44, 696, 3, 3]
         // on 8x8, batch 3: 24.8 us whole, 10.0 in 8 chunks; ResNet-50's last
         // 3x3 at batch 8: 15.5 whole, 13.3 in 4, 17.4 in 8; at batch 64 16.5
@@ -1259,7 +1259,7 @@ void split_plan(const sa_conv_desc &d, const sa_compact_sizes &s, ConvPlan *pl) 
         float best = tile_time(a, tile_pick(a), 1);
         p.ksplit = 1;
         for (int ks = 2; ks <= most; ++ks) {
-            const float sum = 5.0f + (float)ks * (float)p.NPQ * (float)p.Cy * (8e-6f / 0.9f);
+            const float sum = 4.0f + (float)ks * (float)p.NPQ * (float)p.Cy * (8e-6f / 0.9f);
             const float t = tile_time(a, kTileSplit, ks) + sum;
             if (t < best) best = t, p.ksplit = ks;
         }
