@@ -464,11 +464,18 @@ int resident_workgroups(const void *kern, int nt, int lds, int *wgs) {
 
 // Every slice of 64 columns lies in one tap (runs are multiples of 64), at most
 // 31 taps (one bit each), and the input with its padded border below 2 GiB.
+// The loads' scalar offset (last tap and channel) stays within that range too:
+// the unit compares a lane's offset with the range less the scalar offset, which
+// must not fall below zero (a single image smaller than the kernel, where the
+// last taps are padding for every pixel).
 bool uniform_taps(const ConvArgs &a) {
     bool uni = a.C * a.D <= 31;
-    for (int i = 0; i < a.ngroups; ++i)
-        uni = uni && a.g[i].run % kBK == 0 && a.g[i].run > 0 &&
-              (int64_t)a.g[i].x_bytes + (int64_t)a.pad * (a.W + 1) * a.g[i].Cx * 2 < (int64_t(1) << 31);
+    for (int i = 0; i < a.ngroups; ++i) {
+        const ConvGroup &G = a.g[i];
+        const int64_t range = (int64_t)G.x_bytes + (int64_t)a.pad * (a.W + 1) * G.Cx * 2;
+        const int64_t last = (((int64_t)(a.C - 1) * a.W + a.D - 1) * G.Cx + G.run) * 2;
+        uni = uni && G.run % kBK == 0 && G.run > 0 && range < (int64_t(1) << 31) && last <= range;
+    }
     return uni;
 }
 

@@ -23,6 +23,9 @@ CASES = [
     ((3, 64, 8, 10, 17, 3, 3, 1, 3, 1, sa.FILTER, 1.0), D),      # padding wider than the kernel
     ((2, 64, 5, 1, 20, 3, 3, 1, 1, 1, sa.FILTER, 1.0), D),       # one pixel wide
     ((2, 128, 15, 13, 70, 3, 3, 2, 1, 2, sa.FILTER, 0.7), D),    # two groups of 64 channels, stride 2
+    ((1, 64, 1, 1, 40, 3, 3, 1, 1, 1, sa.FILTER, 1.0), D),       # image smaller than the kernel
+    ((1, 64, 2, 1, 40, 5, 5, 1, 2, 1, sa.FILTER, 1.0), D),
+    ((1, 128, 1, 3, 40, 3, 3, 1, 2, 2, sa.FILTER, 1.0), D),
     ((2, 64, 11, 12, 40, 5, 5, 2, 2, 1, sa.FILTER, 1.0), D),     # 25 taps, stride 2
     ((2, 8, 15, 16, 24, 7, 7, 1, 3, 1, sa.FILTER, 1.0), D),      # 49 taps of 8 channels
     ((30, 64, 9, 9, 90, 7, 5, 1, 2, 1, sa.FILTER, 1.0), D),       # 35 taps of 64 channels
