@@ -355,8 +355,8 @@ typedef struct sa_conv_plan_info {
     int32_t ig_tile[4];               /* SA_CONV_DIRECT_IG: MT, NF, WM = 16*MT*WM filters by
                                          64*NF/WM pixels per tile, and 1 (every tile
                                          runs whole in one workgroup of four wavefronts)  */
-    int32_t footprint_tile[3];        /* SA_CONV_FOOTPRINT: TM, TN, NW = 32*TM filters by
-                                         32*NW*TN pixels per workgroup                    */
+    int32_t footprint_tile[3];        /* SA_CONV_FOOTPRINT: FM, TN, NP = 32*FM filters by
+                                         32*NP*TN pixels per workgroup                    */
 } sa_conv_plan_info;
 int structadmm_conv_plan(const sa_conv_desc *desc, sa_conv_plan_info *info);
 

@@ -52,3 +52,28 @@ CASES = [
 @pytest.mark.parametrize("case,expect", CASES, ids=["x".join(str(v) for v in c[:10]) for c, _ in CASES])
 def test_conv_direct_tiles(case, expect):
     conv_case(*case, seed=sum(case[:9]) + 5, dense_too=False, expect=expect)
+
+
+def F(*tile):
+    return {"path": {sa.CONV_FOOTPRINT}, "footprint_tile": tile}
+
+
+# the footprint kernel's shapes with several wavefronts over the filters of one
+# input copy, or 64-pixel tiles: last tiles partly filled in filters and pixels,
+# images that end within a tile, columns that are no whole step of 16.  At least
+# 20 columns: the largest output of a layer with a few passes 10 times the RMS,
+# where the rounding to bf16 alone (2^-9 of it) is past the bar of 2e-2.
+FOOTPRINT = [
+    ((1, 256, 17, 16, 9, 1, 1, 1, 0, 1, sa.SHAPE, 0.2), F(2, 1, 2)),
+    ((17, 512, 11, 10, 568, 1, 1, 1, 0, 2, sa.SHAPE, 0.1), F(4, 1, 2)),
+    ((33, 96, 17, 17, 223, 3, 3, 1, 1, 1, sa.SHAPE, 0.2), F(4, 1, 3)),
+    ((129, 128, 9, 10, 282, 1, 1, 1, 0, 1, sa.SHAPE, 0.2), F(6, 1, 3)),
+    ((65, 48, 17, 17, 816, 3, 3, 2, 1, 2, sa.SHAPE, 0.1), F(8, 1, 3)),
+    ((65, 128, 28, 28, 309, 1, 1, 2, 0, 1, sa.SHAPE, 0.3), F(12, 1, 3)),
+    ((17, 256, 28, 27, 611, 1, 1, 1, 0, 1, sa.SHAPE, 0.1), F(12, 1, 4)),
+]
+
+
+@pytest.mark.parametrize("case,expect", FOOTPRINT, ids=["x".join(str(v) for v in c[:10]) for c, _ in FOOTPRINT])
+def test_conv_footprint_tiles(case, expect):
+    conv_case(*case, seed=sum(case[:9]) + 5, dense_too=False, expect=expect)
