@@ -1246,12 +1246,11 @@ int patch_lds(int TM, int TN, int patch_bytes, int tab_bytes, int NP = 4, int WM
 // fourth root of the sum of fourth powers.  The constants are a least-squares fit of the logarithm to
 // 422 measured layers (random shape- and channel-pruned ones and AlexNet's) in up
 // to 40 shapes each; they scatter by 20%.
-float patch_time(const PatchShape &t, int64_t pb, int64_t lds, int K, int64_t wgs) {
+float patch_time(const PatchShape &t, int64_t pb, int64_t lds, int K, int64_t wgs, int64_t cus) {
     const int waves = t.NP * t.WM;
     // workgroups per CU: 256 registers a lane (512 for tall tiles of few wavefronts) and LDS
     const int64_t by_regs = std::max(1, (t.TM >= 6 && waves <= 4 ? 4 : 8) / waves);
     const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(by_regs, kLdsBytes / std::max<int64_t>(1, lds)));
-    const int64_t cus = device_cus();
     const float steps = (float)((K + 15) / 16), kb = (float)pb / 64e3f;
     const float rounds = (float)((wgs + cus * per_cu - 1) / (cus * per_cu)), load = (float)((wgs + cus - 1) / cus);
     const float serial = 6.31f + 0.996f * (float)pb * 4.0f / (64e3f * waves) +
@@ -1315,11 +1314,11 @@ void split_plan(const sa_conv_desc &d, const sa_compact_sizes &s, ConvPlan *pl) 
         // on 8x8, batch 3: 24.8 us whole, 10.0 in 8 chunks; ResNet-50's last
         // 3x3 at batch 8: 15.5 whole, 13.3 in 4, 17.4 in 8; at batch 64 16.5
         // whole, 25.9 in 2).
-        float best = tile_time(a, tile_pick(a), 1);
+        float best = tile_time(a, tile_pick(a), 1, cus);
         p.ksplit = 1;
         for (int ks = 2; ks <= most; ++ks) {
             const float sum = 4.0f + (float)ks * (float)p.NPQ * (float)p.Cy * (8e-6f / 0.9f);
-            const float t = tile_time(a, kTileSplit, ks) + sum;
+            const float t = tile_time(a, kTileSplit, ks, cus) + sum;
             if (t < best) best = t, p.ksplit = ks;
         }
         if (p.ksplit == 1) return;
@@ -1375,6 +1374,7 @@ void patch_retile(const sa_compact_sizes &s, bool open, ConvPlan *pl) {
     if (!open) return;
     const int Hp = p.gH + 2 * p.gpad, Wp = p.gW + 2 * p.gpad;
     const int Wpp = (Wp + p.gs - 1) / p.gs * p.gs;
+    const int64_t cus = device_cus();
     int K = 0, pix = 0;
     for (int g = 0; g < s.groups; ++g)
         if (p.path[g] == kPatch) K = std::max(K, s.K[g]), pix = std::max(pix, p.pix_bytes[g]);
@@ -1392,7 +1392,7 @@ void patch_retile(const sa_compact_sizes &s, bool open, ConvPlan *pl) {
         for (int g = 0; g < s.groups; ++g)
             if (p.path[g] == kPatch) mt += (s.M[g] + 32 * t.TM * t.WM - 1) / (32 * t.TM * t.WM);
         const int px = 32 * t.NP * t.TN;
-        const float time = patch_time(t, pb, lds, K, mt * ((p.NPQ + px - 1) / px));
+        const float time = patch_time(t, pb, lds, K, mt * ((p.NPQ + px - 1) / px), cus);
         if (t.TM == p.TM && t.TN == p.TN && t.NP == p.NP && t.WM == p.WM) now_t = time;
         if (t.TN == 1 && t.NP <= 4 && (best_t == 0 || time < best_t)) {
             best_t = time;

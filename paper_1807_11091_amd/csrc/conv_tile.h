@@ -17,8 +17,8 @@ constexpr int kConv128x64 = 8;   // k_conv, 128 pixels x 64 filters
 
 // Time in microseconds that the model expects of one launch for every group of
 // a (its pixels, groups, columns and input; split over ksplit chunks of
-// columns) with shape `row`.
-float tile_time(const ConvArgs &a, int row, int ksplit);
+// columns) with shape `row` on cus CUs.
+float tile_time(const ConvArgs &a, int row, int ksplit, int64_t cus);
 // The fastest shape by that model.
 int tile_pick(const ConvArgs &a);
 // Launches every group of a with k_conv_tile shape `row` < kTileShapes (with

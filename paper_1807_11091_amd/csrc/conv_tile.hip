@@ -557,9 +557,9 @@ constexpr Model kModel[2][9] = {
 
 }  // namespace
 
-float tile_time(const ConvArgs &a, int row, int ksplit) {
+float tile_time(const ConvArgs &a, int row, int ksplit, int64_t cus) {
     const Model &m = kModel[uniform_taps(a) ? 0 : 1][row];
-    const int64_t cus = device_cus(), pt = (a.NPQ + m.BM - 1) / m.BM;
+    const int64_t pt = (a.NPQ + m.BM - 1) / m.BM;
     int64_t tiles = 0, x_bytes = 0, y_bytes = 0;
     int ldk = 0;
     for (int i = 0; i < a.ngroups; ++i) {
@@ -579,6 +579,7 @@ float tile_time(const ConvArgs &a, int row, int ksplit) {
 
 int tile_pick(const ConvArgs &a) {
     const float margin = uniform_taps(a) ? 1.0f / 0.95f : 1.0f / 0.9f;
+    const int64_t cus = device_cus();
     int best = 0;
     float best_t = 0;
     for (int row = 0; row < 9; ++row) {
@@ -586,7 +587,7 @@ int tile_pick(const ConvArgs &a) {
         // faster than k_conv, 10% over mixed taps (few slices, where k_conv
         // often wins): with these margins 2 of the 244 layers run over 5%
         // slower than k_conv, without them 19
-        const float t = tile_time(a, row, 1) * (row < kTileShapes ? margin : 1.0f);
+        const float t = tile_time(a, row, 1, cus) * (row < kTileShapes ? margin : 1.0f);
         if (row == 0 || t < best_t) best = row, best_t = t;
     }
     return best;

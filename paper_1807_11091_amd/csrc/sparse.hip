@@ -45,6 +45,7 @@
 #include <set>
 #include <utility>
 
+#include "conv_ig.h"
 #include "conv_tile.h"
 #include "sa_device.h"
 #include "sa_host.h"
@@ -553,9 +554,10 @@ int sp_plan(const sa_sparse_conv_desc &d, SpPlan *p) {
     p->ws_dense = p->ws_need;
     if (d.B % 8 == 0 && d.groups <= SA_MAX_CONV_GROUPS && (int64_t)d.A * p->ldk < (int64_t(1) << 30)) {
         const ConvArgs a = sp_conv_args(d, *p, nullptr);
+        const int64_t cus = device_cus();
         float best = 0;
         for (int row = 0; row < kTileShapes; ++row) {
-            const float t = tile_time(a, row, 1);
+            const float t = tile_time(a, row, 1, cus);
             if (row == 0 || t < best) best = t, p->row = row;
         }
         const float guard = 4.0f + (float)NPQ * (float)d.A * 2e-6f / 5.0f;
