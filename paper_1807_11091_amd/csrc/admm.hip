@@ -1200,8 +1200,14 @@ int project_impl(const sa_project_desc *layers, int n_layers, void *ws, size_t w
             return p && q && (uintptr_t)p < (uintptr_t)(q + nb) && (uintptr_t)q < (uintptr_t)(p + na);
         };
         const sa_project_desc &b = l[ids[m]];
+        // a's mask [n] and b's support [groups * B], where one starts inside the other
+        auto reads = [](const sa_project_desc &a, const sa_project_desc &b) {
+            const uintptr_t k = (uintptr_t)a.mask, s = (uintptr_t)b.in_ch_mask;
+            return s && k < s + (uint64_t)b.groups * b.B && s < k + (uint64_t)(a.A * a.B * a.C * a.D);
+        };
         for (int j = 0; j < m; ++j) {
             const sa_project_desc &a = l[ids[j]];
+            if (reads(a, b) || reads(b, a)) return false;
             for (const float *w : {(const float *)a.Z, (const float *)a.G, (const float *)(a.G ? a.U : nullptr)})
                 for (const float *t : {b.W, (const float *)b.U, (const float *)b.Z, (const float *)b.G})
                     if (meet(a, w, b, t)) return false;
