@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
@@ -1083,6 +1084,29 @@ T *ws_at(void *ws, size_t off) {
 
 int launch_check(const char *what) { return check_hip(hipGetLastError(), what); }
 
+// Bytes [lo, hi) of a buffer; empty for a null pointer.
+struct Span {
+    uintptr_t lo, hi;
+};
+Span span(const void *p, int64_t bytes) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+    return p ? Span{a, a + (uintptr_t)bytes} : Span{0, 0};
+}
+bool meet(const Span &a, const Span &b) { return a.lo < b.hi && b.lo < a.hi; }
+
+int64_t entries(const sa_project_desc &d) { return d.A * d.B * d.C * d.D; }
+
+// What the projection of a layer writes, and what it reads.
+std::array<Span, 6> written(const sa_project_desc &d) {
+    const int64_t n = d.A * d.B * d.C * d.D, g = n_groups(d);
+    return {span(d.Z, n * 4), span(d.mask, g),    span(d.kept_idx, d.k * 4), span(d.scores, g * 8),
+            span(d.G, n * 4), span(d.G ? d.U : nullptr, n * 4)};
+}
+std::array<Span, 3> read(const sa_project_desc &d) {
+    const int64_t n = d.A * d.B * d.C * d.D;
+    return {span(d.W, n * 4), span(d.U, n * 4), span(d.in_ch_mask, (int64_t)d.groups * d.B)};
+}
+
 }  // namespace
 }  // namespace sa
 
@@ -1195,25 +1219,16 @@ int project_impl(const sa_project_desc *layers, int n_layers, void *ws, size_t w
     // May layer ids[m] share launches with layers ids[0..m)?  Layers of a level
     // run in the order given where one writes what another reads or writes.
     auto apart = [](const sa_project_desc *l, const int *ids, int m) {
-        auto meet = [](const sa_project_desc &a, const float *p, const sa_project_desc &b, const float *q) {
-            const int64_t na = a.A * a.B * a.C * a.D, nb = b.A * b.B * b.C * b.D;
-            return p && q && (uintptr_t)p < (uintptr_t)(q + nb) && (uintptr_t)q < (uintptr_t)(p + na);
+        auto any = [](const auto &x, const auto &y) {
+            for (const Span &p : x)
+                for (const Span &q : y)
+                    if (meet(p, q)) return true;
+            return false;
         };
         const sa_project_desc &b = l[ids[m]];
-        // a's mask [n] and b's support [groups * B], where one starts inside the other
-        auto reads = [](const sa_project_desc &a, const sa_project_desc &b) {
-            const uintptr_t k = (uintptr_t)a.mask, s = (uintptr_t)b.in_ch_mask;
-            return s && k < s + (uint64_t)b.groups * b.B && s < k + (uint64_t)(a.A * a.B * a.C * a.D);
-        };
         for (int j = 0; j < m; ++j) {
             const sa_project_desc &a = l[ids[j]];
-            if (reads(a, b) || reads(b, a)) return false;
-            for (const float *w : {(const float *)a.Z, (const float *)a.G, (const float *)(a.G ? a.U : nullptr)})
-                for (const float *t : {b.W, (const float *)b.U, (const float *)b.Z, (const float *)b.G})
-                    if (meet(a, w, b, t)) return false;
-            for (const float *w : {(const float *)b.Z, (const float *)b.G, (const float *)(b.G ? b.U : nullptr)})
-                for (const float *t : {a.W, (const float *)a.U})
-                    if (meet(b, w, a, t)) return false;
+            if (any(written(a), written(b)) || any(written(a), read(b)) || any(written(b), read(a))) return false;
         }
         return true;
     };

@@ -291,3 +291,30 @@ def test_project_element_mask_off_alignment_and_chained_buffers():
     got = run_project([first, second])
     check(got[0], r1, sa.ELEMENT, k1, True, "first")
     check(got[1], r2, sa.ELEMENT, k2, True, "second")
+
+
+@pytest.mark.parametrize("what", ["mask", "kept", "scores"])
+def test_project_element_layers_share_an_output(what):
+    """Layers of one call that write the same buffer (a mask, kept list or scores
+    that the caller does not read per layer): it holds what the calls one after
+    the other leave, the last layer's values up to its own length."""
+    rng = np.random.default_rng(47)
+    specs = [((48, 40, 3, 3), 0.6), ((40, 30, 3, 3), 0.3), ((33, 17, 3, 3), 0.5)]
+    layers, refs = [], []
+    for shape, part in specs:
+        W, U = element_case(shape, 1, rng)
+        k = int(W.size * part)
+        refs.append(oracle_ref(W, U, sa.ELEMENT, k, rho=1e-3, fused=True))
+        layers.append(GpuLayer(W, U, sa.ELEMENT, k, rho=1e-3, fused=True))
+    for L in layers[1:]:
+        setattr(L, what, getattr(layers[0], what))
+        L.layer = sa.ProjectLayer(L.W, L.U, L.Z, L.mask, L.kept, sa.ELEMENT, L.k, 1, None, L.scores, 1e-3, L.G)
+    key = {"mask": "mask", "kept": "kept_idx", "scores": "scores"}[what]
+    want = np.empty_like(refs[0][key])
+    for r in refs:
+        want[: len(r[key])] = r[key]
+    got = run_project(layers)
+    assert np.array_equal(getattr(layers[0], what).cpu().numpy(), want), what
+    for i, (g, r) in enumerate(zip(got, refs)):
+        g[key] = r[key]  # the shared one, checked above
+        check(g, r, sa.ELEMENT, layers[i].k, True, f"layer {i}")
