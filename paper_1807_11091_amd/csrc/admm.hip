@@ -5,7 +5,8 @@
 //
 // Data flow of structadmm_project for one dependency level of layers:
 //   k_expand_allowed  (channel and shape layers with an input-channel support)
-//                     per-column support bytes; the other sets read the mask
+//                     per-column support bytes; the other sets read the mask, an
+//                     element-wise layer a copy of it if the level overwrites it
 //   k_row_scores      filter sets: one wavefront per weight row, O_a in binary64
 //   k_col_partials    channel / shape sets: binary64 column sums per band of rows
 //   k_select          one workgroup per structured layer: final scores, radix
@@ -1092,19 +1093,24 @@ Span span(const void *p, int64_t bytes) {
     const uintptr_t a = reinterpret_cast<uintptr_t>(p);
     return p ? Span{a, a + (uintptr_t)bytes} : Span{0, 0};
 }
-bool meet(const Span &a, const Span &b) { return a.lo < b.hi && b.lo < a.hi; }
+template <size_t M, size_t N>
+bool meet(const std::array<Span, M> &a, const std::array<Span, N> &b) {
+    for (const Span &p : a)
+        for (const Span &q : b)
+            if (p.lo < q.hi && q.lo < p.hi) return true;
+    return false;
+}
 
 int64_t entries(const sa_project_desc &d) { return d.A * d.B * d.C * d.D; }
 
-// What the projection of a layer writes, and what it reads.
+// What the projection of a layer writes, and what it reads besides its support.
 std::array<Span, 6> written(const sa_project_desc &d) {
-    const int64_t n = d.A * d.B * d.C * d.D, g = n_groups(d);
+    const int64_t n = entries(d), g = n_groups(d);
     return {span(d.Z, n * 4), span(d.mask, g),    span(d.kept_idx, d.k * 4), span(d.scores, g * 8),
             span(d.G, n * 4), span(d.G ? d.U : nullptr, n * 4)};
 }
-std::array<Span, 3> read(const sa_project_desc &d) {
-    const int64_t n = d.A * d.B * d.C * d.D;
-    return {span(d.W, n * 4), span(d.U, n * 4), span(d.in_ch_mask, (int64_t)d.groups * d.B)};
+std::array<Span, 2> read(const sa_project_desc &d) {
+    return {span(d.W, entries(d) * 4), span(d.U, entries(d) * 4)};
 }
 
 }  // namespace
@@ -1219,16 +1225,10 @@ int project_impl(const sa_project_desc *layers, int n_layers, void *ws, size_t w
     // May layer ids[m] share launches with layers ids[0..m)?  Layers of a level
     // run in the order given where one writes what another reads or writes.
     auto apart = [](const sa_project_desc *l, const int *ids, int m) {
-        auto any = [](const auto &x, const auto &y) {
-            for (const Span &p : x)
-                for (const Span &q : y)
-                    if (meet(p, q)) return true;
-            return false;
-        };
         const sa_project_desc &b = l[ids[m]];
         for (int j = 0; j < m; ++j) {
             const sa_project_desc &a = l[ids[j]];
-            if (any(written(a), written(b)) || any(written(a), read(b)) || any(written(b), read(a))) return false;
+            if (meet(written(a), written(b)) || meet(written(a), read(b)) || meet(written(b), read(a))) return false;
         }
         return true;
     };
@@ -1260,16 +1260,28 @@ int project_impl(const sa_project_desc *layers, int n_layers, void *ws, size_t w
         for (int i = 0; i < n_layers; ++i)
             if (level[i] == lv) ids.push_back(i);
 
-        // allowed bytes for layers with a channel support (filter and
-        // element-wise sets read the mask itself)
+        // Allowed bytes for layers with a channel support (filter sets read the
+        // mask itself).  An element-wise layer reads the mask itself too, unless
+        // a layer of this level writes over it (its own mask, one that a later
+        // layer selects, a place inside another buffer): then it reads a copy
+        // from before the level, one byte per channel.
+        std::vector<char> held(n_layers, 0);
         for (int i : ids) {
             const sa_project_desc &d = layers[i];
-            if (!d.in_ch_mask || d.kind == SA_FILTER || d.kind == SA_ELEMENT) continue;
+            if (!d.in_ch_mask || d.kind == SA_FILTER) continue;
             const LayerPlan &p = plan[i];
-            int64_t total = (int64_t)d.groups * p.K;
+            int K = p.K, CD = p.CD;
+            if (d.kind == SA_ELEMENT) {
+                const std::array<Span, 1> sup = {span(d.in_ch_mask, (int64_t)d.groups * d.B)};
+                for (int j : ids) held[i] = held[i] || meet(sup, written(layers[j]));
+                if (!held[i]) continue;
+                K = (int)d.B;
+                CD = 1;
+            }
+            int64_t total = (int64_t)d.groups * K;
             int blocks = (int)std::min<int64_t>(1024, (total + 255) / 256);
             hipLaunchKernelGGL(k_expand_allowed, dim3(blocks), dim3(256), 0, stream, d.in_ch_mask,
-                               ws_at<uint8_t>(ws, p.off_allowed), d.groups, (int)d.B, p.CD, p.K);
+                               ws_at<uint8_t>(ws, p.off_allowed), d.groups, (int)d.B, CD, K);
             if (int rc = launch_check("k_expand_allowed")) return rc;
         }
 
@@ -1384,7 +1396,7 @@ int project_impl(const sa_project_desc *layers, int n_layers, void *ws, size_t w
                     a.mask = d.mask;
                     a.kept_idx = d.kept_idx;
                     a.scores = d.scores;
-                    a.inmask = d.in_ch_mask;
+                    a.inmask = held[el[s + t]] ? ws_at<uint8_t>(ws, p.off_allowed) : d.in_ch_mask;
                     char *eb = ws_at<char>(ws, p.off_elem);
                     a.hist = reinterpret_cast<uint32_t *>(eb);
                     a.state = reinterpret_cast<ElemState *>(eb + sizeof(uint32_t) * 3 * 2048);

@@ -318,3 +318,33 @@ def test_project_element_layers_share_an_output(what):
     for i, (g, r) in enumerate(zip(got, refs)):
         g[key] = r[key]  # the shared one, checked above
         check(g, r, sa.ELEMENT, layers[i].k, True, f"layer {i}")
+
+
+@pytest.mark.parametrize("groups", [1, 2])
+@pytest.mark.parametrize("place", ["own mask", "later filter layer", "later element layer", "inside a filter layer",
+                                   "inside an element layer"])
+def test_project_element_support_overwritten_in_its_level(place, groups):
+    """An element-wise layer whose support bytes are written by a layer of the
+    same level (only the very mask of an earlier layer orders the two): it is
+    projected within the support that the call finds there."""
+    rng = np.random.default_rng(53)
+    shape = (24, 20, 3, 3)
+    W, U = element_case(shape, groups, rng)
+    m = (rng.random(groups * shape[1]) < 0.5).astype(np.uint8)
+    k = int(W.size * 0.4)
+    ref = oracle_ref(W, U, sa.ELEMENT, k, groups, in_ch_mask=m, rho=1e-3, fused=True)
+    layer = GpuLayer(W, U, sa.ELEMENT, k, groups, rho=1e-3, fused=True)
+    kind = sa.ELEMENT if "element" in place else sa.FILTER
+    oW, oU = element_case((groups * shape[1] + 30, 5, 3, 3), 1, rng)
+    ok = n_groups(oW.shape, kind) // 2
+    oref = oracle_ref(oW, oU, kind, ok, rho=1e-3, fused=True)
+    other = GpuLayer(oW, oU, kind, ok, rho=1e-3, fused=True)
+    host = layer.mask if place == "own mask" else other.mask
+    support = host[13 if "inside" in place else 0:][: len(m)]
+    support.copy_(to_dev(m))
+    layer.layer = sa.ProjectLayer(layer.W, layer.U, layer.Z, layer.mask, layer.kept, sa.ELEMENT, k, groups, support,
+                                  layer.scores, 1e-3, layer.G)
+    order = [other, layer] if "inside" in place else [layer, other]
+    got = run_project(order)
+    check(got[order.index(layer)], ref, sa.ELEMENT, k, True, place)
+    check(got[order.index(other)], oref, kind, ok, True, "other layer")
