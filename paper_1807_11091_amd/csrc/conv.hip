@@ -1055,19 +1055,34 @@ bool is_vec(const sa_compact_sizes &s, int g, int Cx) {
     return s.run[g] > 0 && s.run[g] % 8 == 0 && s.run_base[g] % 8 == 0 && Cx % 8 == 0;
 }
 
-// Footprint of the largest output tile of BM pixels: padded input rows.
+// Footprint of the largest output tile of BM pixels: padded input rows.  A
+// tile's rows depend on its start within an image alone, and the starts there
+// are the multiples of g = gcd(BM, P*Q) once enough images follow one another.
+// The last start of an output row reaches furthest down, and no start further
+// than one at the last pixel of the first or last row of an image: at most P
+// steps, mostly a few, where a large image has thousands of tiles (89 x 89,
+// batch 88: a plan took 390 us with a step per tile, 4 us so, with each
+// tile width once).
 int patch_rows(int NPQ, int P, int Q, int Hp, int stride, int C, int BM) {
-    int best = 0, a = BM, b = P * Q;
-    while (b) std::swap(a %= b, b);  // a: their greatest common divisor
-    // a tile's rows depend on its start within an image alone: one period
-    const int64_t end = std::min<int64_t>(NPQ, (int64_t)BM * (P * Q / a));
-    for (int64_t n = 0; n < end; n += BM) {
-        const int n0 = (int)n;
-        const int r0 = n0 / Q, r1 = (int)((std::min<int64_t>(n + BM, NPQ) - 1) / Q);
-        const int g0 = (r0 / P) * Hp + (r0 % P) * stride;
-        const int g1 = (r1 / P) * Hp + (r1 % P) * stride + C;
-        best = std::max(best, g1 - g0);
+    const uint32_t uP = P, uQ = Q, PQ = uP * uQ, end = NPQ;  // below 2^31, so sums with BM stay below 2^32
+    uint32_t g = BM, b = PQ;
+    while (b) std::swap(g %= b, b);
+    auto rows = [&](uint32_t n, uint32_t last) {
+        const uint32_t r0 = n / uQ, r1 = last / uQ, i0 = r0 / uP, i1 = r1 / uP;
+        return (int)(i1 - i0) * Hp + ((int)(r1 - i1 * uP) - (int)(r0 - i0 * uP)) * stride + C;
+    };
+    int most = std::max(rows(uQ - 1, uQ + BM - 2), rows(PQ - 1, PQ + BM - 2)), best = 0;
+    if (end / BM >= uP) {
+        for (uint32_t r = uP; r > 0 && best < most; --r) {
+            const uint32_t n = (r * uQ - 1) / g * g;
+            if (n >= (r - 1) * uQ) best = std::max(best, rows(n, n + BM - 1));
+        }
+        if (end / BM >= PQ / g) return best;
+        most = best;
+        best = 0;
     }
+    // too few tiles to meet every start
+    for (uint32_t n = 0; n < end && best < most; n += BM) best = std::max(best, rows(n, std::min(n + BM, end) - 1));
     return best;
 }
 
@@ -1359,6 +1374,13 @@ void direct_plan(const sa_compact_sizes &s, ConvPlan *pl) {
     p.direct_ig = maxM <= 64 && coarse * 100 >= fine * 115 && maxK >= 384 && maxK <= 512 && p.NPQ >= (1 << 16);
 }
 
+// patch_rows of a tile of 32 * frags pixels (frags <= 8), worked out once per
+// plan: `rows` starts as zeros.
+int tile_rows(const ConvPlan &p, int frags, int (&rows)[9]) {
+    if (rows[frags] == 0) rows[frags] = patch_rows(p.NPQ, p.P, p.Q, p.gH + 2 * p.gpad, p.gs, p.gC, 32 * frags);
+    return rows[frags];
+}
+
 // Replaces the chosen footprint shape by the one that patch_time expects to be
 // fastest, where that is at least 8% ahead (the scatter of the model between
 // two shapes of a layer).  The rules before it look for the least padded filter
@@ -1369,22 +1391,22 @@ void direct_plan(const sa_compact_sizes &s, ConvPlan *pl) {
 // few-channel layers on a space-to-depth image are not in it).  Tiles of more
 // than 128 pixels are left to the rules before it (choosing them here too would
 // take 0.91).
-void patch_retile(const sa_compact_sizes &s, bool open, ConvPlan *pl) {
+void patch_retile(const sa_compact_sizes &s, bool open, int (&rows)[9], ConvPlan *pl) {
     ConvPlan &p = *pl;
     if (!open) return;
-    const int Hp = p.gH + 2 * p.gpad, Wp = p.gW + 2 * p.gpad;
+    const int Wp = p.gW + 2 * p.gpad;
     const int Wpp = (Wp + p.gs - 1) / p.gs * p.gs;
     const int64_t cus = device_cus();
     int K = 0, pix = 0;
     for (int g = 0; g < s.groups; ++g)
         if (p.path[g] == kPatch) K = std::max(K, s.K[g]), pix = std::max(pix, p.pix_bytes[g]);
-    int rows[9] = {};  // padded input rows by 32-pixel fragments of the tile
     ConvPlan best = p;
     float best_t = 0, now_t = 0;
     for (const PatchShape &t : kPatchShapes) {
-        int &r = rows[t.NP * t.TN];
-        if (r == 0) r = patch_rows(p.NPQ, p.P, p.Q, Hp, p.gs, p.gC, 32 * t.NP * t.TN);
-        const int64_t pb = ((int64_t)r * Wpp * pix + 15) / 16 * 16;
+        const bool now = t.TM == p.TM && t.TN == p.TN && t.NP == p.NP && t.WM == p.WM;
+        const bool candidate = t.TN == 1 && t.NP <= 4;
+        if (!now && !candidate) continue;
+        const int64_t pb = ((int64_t)tile_rows(p, t.NP * t.TN, rows) * Wpp * pix + 15) / 16 * 16;
         if (pb > kLdsBytes) continue;
         const int lds = patch_lds(t.TM, t.TN, (int)pb, p.tab_bytes, t.NP, t.WM);
         if (lds > kLdsBytes) continue;
@@ -1393,8 +1415,8 @@ void patch_retile(const sa_compact_sizes &s, bool open, ConvPlan *pl) {
             if (p.path[g] == kPatch) mt += (s.M[g] + 32 * t.TM * t.WM - 1) / (32 * t.TM * t.WM);
         const int px = 32 * t.NP * t.TN;
         const float time = patch_time(t, pb, lds, K, mt * ((p.NPQ + px - 1) / px), cus);
-        if (t.TM == p.TM && t.TN == p.TN && t.NP == p.NP && t.WM == p.WM) now_t = time;
-        if (t.TN == 1 && t.NP <= 4 && (best_t == 0 || time < best_t)) {
+        if (now) now_t = time;
+        if (candidate && (best_t == 0 || time < best_t)) {
             best_t = time;
             best.TM = t.TM;
             best.TN = t.TN;
@@ -1508,8 +1530,9 @@ int conv_plan(const sa_conv_desc &d, ConvPlan *pl) {
         // 32-filter blocks (measured on the 13x13 AlexNet layers) plus one
         // unit per 32-filter block; TM >= 6 runs one workgroup per CU
         // (registers), smaller tiles up to two (LDS permitting)
-        const int Hp = p.gH + 2 * p.gpad, Wp = p.gW + 2 * p.gpad;
+        const int Wp = p.gW + 2 * p.gpad;
         const int Ws = (Wp + p.gs - 1) / p.gs, Wpp = Ws * p.gs;
+        int tile_row[9] = {};
         p.tab_bytes = ((max_ldk + 2 * kPatchSlice) * 4 + 15) / 16 * 16;  // two slices past the last
         int64_t least = -1;
         for (int tm : kPatchTMs) {
@@ -1518,7 +1541,7 @@ int conv_plan(const sa_conv_desc &d, ConvPlan *pl) {
                 if (p.path[g] == kPatch) cost += (s.M[g] + 32 * tm - 1) / (32 * tm) * (32 * tm);
             if (least < 0 || cost < least) least = cost;
         }
-        const int rows128 = patch_rows(p.NPQ, p.P, p.Q, Hp, p.gs, p.gC, 128);
+        const int rows128 = tile_rows(p, 4, tile_row);
         int64_t pb128 = 0;
         for (int g = 0; g < s.groups; ++g)
             if (p.path[g] == kPatch)
@@ -1541,7 +1564,7 @@ int conv_plan(const sa_conv_desc &d, ConvPlan *pl) {
         }
         p.TM = best_tm;
         auto fits = [&](int tn, int *patch_bytes) {
-            const int rows = patch_rows(p.NPQ, p.P, p.Q, Hp, p.gs, p.gC, 128 * tn);
+            const int rows = tile_rows(p, 4 * tn, tile_row);
             int64_t pb = 0;
             for (int g = 0; g < s.groups; ++g)
                 if (p.path[g] == kPatch) pb = std::max<int64_t>(pb, ((int64_t)rows * Wpp * p.pix_bytes[g] + 15) / 16 * 16);
@@ -1572,7 +1595,7 @@ int conv_plan(const sa_conv_desc &d, ConvPlan *pl) {
             // is partly filled (AlexNet conv4/conv5: 338 tiles) can take one round
             // fewer, each workgroup about 1.5 times as long
             if (p.TN == 1 && (p.TM == 6 || p.TM == 4)) {
-                const int rows6 = patch_rows(p.NPQ, p.P, p.Q, Hp, p.gs, p.gC, 192);
+                const int rows6 = tile_rows(p, 6, tile_row);
                 int64_t pb6 = 0;
                 for (int g = 0; g < s.groups; ++g)
                     if (p.path[g] == kPatch) pb6 = std::max<int64_t>(pb6, ((int64_t)rows6 * Wpp * p.pix_bytes[g] + 15) / 16 * 16);
@@ -1589,7 +1612,7 @@ int conv_plan(const sa_conv_desc &d, ConvPlan *pl) {
                     }
                 }
             }
-            patch_retile(s, p.s2d <= 1, &p);
+            patch_retile(s, p.s2d <= 1, tile_row, &p);
         } else {
             for (int g = 0; g < s.groups; ++g)
                 if (p.path[g] == kPatch) p.path[g] = kGather;
