@@ -54,12 +54,17 @@ __device__ inline i32x4 dma_rsrc(const void *base, uint32_t bytes) {
     return i32x4{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xffffu), (int)bytes, kRsrcWord3};
 }
 // 16 bytes per lane straight from memory to LDS: lane i's land at lds + 16 * i
-// (M0 holds the LDS address; nothing else in the kernel uses M0)
+// (M0 holds the LDS address).  M0 is declared, so that the compiler lets no use
+// of its own rest on a value from before the statement; its warning says that a
+// reserved register is not saved around the asm, which nothing here needs.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ inline void dma16(i32x4 r, uint32_t voff, uint32_t soff, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff),
                  "s"(r), "s"(soff)
-                 : "memory");
+                 : "memory", "m0");
 }
+#pragma clang diagnostic pop
 template <int N>
 __device__ inline void wait_vm() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");

@@ -390,3 +390,16 @@ def test_product_path_has_no_oracle_dependency():
                 text = open(os.path.join(dirpath, f)).read()
                 assert "import oracle" not in text and "from oracle" not in text, f
                 assert "oracle.h" not in text and "liboracle" not in text, f
+
+
+def test_inline_asm_declares_what_it_writes():
+    """Every inline asm statement that writes M0 names it among its clobbers."""
+    csrc = os.path.join(ROOT, "paper_1807_11091_amd", "csrc")
+    seen = 0
+    for f in os.listdir(csrc):
+        if f.endswith((".hip", ".h")):
+            for stmt in re.findall(r"\basm\b[^;]*;", open(os.path.join(csrc, f)).read()):
+                if "s_mov_b32 m0" in stmt:
+                    seen += 1
+                    assert re.search(r':[^:]*"m0"[^:]*\);$', stmt), (f, stmt)
+    assert seen > 0
