@@ -1323,16 +1323,20 @@ void split_plan(const sa_conv_desc &d, const sa_compact_sizes &s, ConvPlan *pl) 
     if (most < 2 || (int64_t)min_sl * (most - 1) <= 20 * most) return;
     p.ksplit = most;
     if (ng == 0) {
-        // The split that the time model expects to be fastest, the second
-        // pass and its launch at 4 us plus the partial sums written and read
-        // at 0.9 TB/s (fitted on layers of 192 to 12,544 pixels: [44, 696, 3, 3]
-        // on 8x8, batch 3: 24.8 us whole, 10.0 in 8 chunks; ResNet-50's last
-        // 3x3 at batch 8: 15.5 whole, 13.3 in 4, 17.4 in 8; at batch 64 16.5
-        // whole, 25.9 in 2).
+        // The split that the time model expects to be fastest: the second pass
+        // at 2 us, or 1 us for 8 chunks (all of them loaded at once), plus the
+        // partial sums written and read at 1.6 TB/s.  Fitted on the GPU time of
+        // 133 layers of 9 to 4300 pixels in 1 to 8 chunks each (launches one
+        // after the other in a graph): the choice takes 1.007 of the time of
+        // the best count, one layer in 133 over 3% longer than unsplit (4 us
+        // and 0.9 TB/s took 1.078).  [253, 168, 3, 3], stride 2, batch 13:
+        // 9.6 us whole, 7.2 in 8 chunks; [433, 152, 5, 5] on 14x14, batch 2:
+        // 18.0 whole, 12.5 in 4, 15.2 in 8; [384, 256, 3, 3] on 13x13, batch 1:
+        // 9.4 whole, 9.1 in 8.
         float best = tile_time(a, tile_pick(a), 1, cus);
         p.ksplit = 1;
         for (int ks = 2; ks <= most; ++ks) {
-            const float sum = 4.0f + (float)ks * (float)p.NPQ * (float)p.Cy * (8e-6f / 0.9f);
+            const float sum = (ks == 8 ? 1.0f : 2.0f) + (float)ks * (float)p.NPQ * (float)p.Cy * (8e-6f / 1.6f);
             const float t = tile_time(a, kTileSplit, ks, cus) + sum;
             if (t < best) best = t, p.ksplit = ks;
         }

@@ -305,6 +305,29 @@ def test_conv_plan_host_only():
     assert L.structadmm_conv_plan(ctypes.byref(d), None) == -1
 
 
+@pytest.mark.parametrize("layer,chunks", [
+    # N, H, Cx, taps, stride, filters: GPU time whole, in the chunks asked for here (microseconds)
+    ((13, 4, 168, 3, 2, 253), {8}),       # 9.6, 7.2
+    ((3, 12, 208, 3, 2, 122), {8}),       # 10.8, 7.4
+    ((10, 5, 80, 5, 1, 108), {8}),        # 11.1, 7.7
+    ((2, 14, 152, 5, 1, 433), {3, 4, 5}),  # 18.0, 12.5 (15.2 in 8)
+    ((1, 7, 512, 3, 1, 512), {8}),        # 14.4, 8.7
+    ((64, 14, 256, 3, 1, 256), {1}),      # enough tiles for every CU
+])
+def test_conv_plan_splits_small_launches(layer, chunks):
+    """Layers of few tiles and many columns run in the number of chunks that
+    was measured faster than the whole (256 CUs)."""
+    N, H, Cx, t, stride, M = layer
+    L = sa.lib()
+    s = sa.CompactSizes()
+    K = t * t * Cx
+    s.groups, s.M[0], s.K[0], s.ldk[0], s.run[0], s.ch_span[0] = 1, M, K, (K + 63) // 64 * 64, Cx, Cx
+    d = sa.ConvDesc(N, H, H, Cx, t, t, stride, t // 2, ctypes.pointer(s), FAKE, FAKE, FAKE, FAKE, FAKE, None, 0)
+    info = sa.ConvPlanInfo()
+    assert L.structadmm_conv_plan(ctypes.byref(d), ctypes.byref(info)) == 0
+    assert info.path[0] == sa.CONV_DIRECT and info.ksplit in chunks, info.ksplit
+
+
 def test_conv_plan_host_time_of_many_tiles():
     """The host's part of a footprint layer does not grow with its pixel tiles:
     88 images of 89x89 (an odd size: tiles start at thousands of places within
