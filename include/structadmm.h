@@ -360,6 +360,24 @@ typedef struct sa_conv_plan_info {
 } sa_conv_plan_info;
 int structadmm_conv_plan(const sa_conv_desc *desc, sa_conv_plan_info *info);
 
+/* The tile shapes of that plan, for programs that log or test which kernel a
+ * layer takes: every field 0 for a path that no group takes.  Host only, same
+ * validation and error codes as structadmm_conv_plan. */
+typedef struct sa_conv_tile_info {
+    int32_t direct_pixels;    /* SA_CONV_DIRECT: pixels by filters of a tile             */
+    int32_t direct_filters;
+    int32_t direct_fetchers;  /* wavefronts that fetch operands (k_conv_tile), or 0: the
+                                 wavefronts that multiply fetch for themselves (k_conv)  */
+    int32_t direct_slices;    /* slices of 64 columns that the LDS holds                 */
+    int32_t direct_one_tap;   /* k_conv_tile: 1 when every slice lies in one tap of the
+                                 kernel, 0 when slices run on from tap to tap            */
+    int32_t footprint_pixels; /* SA_CONV_FOOTPRINT: pixels by filters of a tile          */
+    int32_t footprint_filters;
+    int32_t footprint_pixel_waves;  /* wavefronts over the pixels, over the filters      */
+    int32_t footprint_filter_waves;
+} sa_conv_tile_info;
+int structadmm_conv_tiles(const sa_conv_desc *desc, sa_conv_tile_info *info);
+
 /* ---- non-structured layers as CSR: structadmm_csr -------------------- */
 /*
  * The non-structured set of Section 3 keeps an arbitrary pattern of weights,

@@ -13,6 +13,7 @@ Entry points (same names as the C ABI):
   compact(Z, groups, ..., ws=None, stream=None) -> (Wc, row_idx, col_ch, col_tap, sizes)
   pack_nhwc(X, keep=None, Cx=None, stream=None)
   conv_fwd(X, Wc, col_ch, col_tap, sizes, C, D, stride, pad, Y=None, stream=None, ldy=None)
+  conv_plan / conv_tiles(Xp, sizes, C, D, stride, pad) -> dict
   csr(Z, kept_idx, row_ptr=None, col=None, val=None, stream=None) -> (row_ptr, col, val)
   conv_sparse_workspace(Xp, shape, groups, stride, pad, nnz)
   conv_sparse_fwd(Xp, row_ptr, col, val, shape, groups, stride, pad, Y=None, ws=None, stream=None)
@@ -93,6 +94,12 @@ class ConvPlanInfo(ctypes.Structure):
                 ("footprint_tile", ctypes.c_int32 * 3)]
 
 
+class ConvTileInfo(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in (
+        "direct_pixels", "direct_filters", "direct_fetchers", "direct_slices", "direct_one_tap",
+        "footprint_pixels", "footprint_filters", "footprint_pixel_waves", "footprint_filter_waves")]
+
+
 # kernel paths of structadmm_conv_plan
 CONV_NONE, CONV_DIRECT, CONV_DIRECT_IG, CONV_FOOTPRINT, CONV_GATHER = 0, 1, 2, 3, 4
 
@@ -147,6 +154,8 @@ def lib():
         L.structadmm_conv_fwd.restype = ctypes.c_int
         L.structadmm_conv_plan.argtypes = [ctypes.POINTER(ConvDesc), ctypes.POINTER(ConvPlanInfo)]
         L.structadmm_conv_plan.restype = ctypes.c_int
+        L.structadmm_conv_tiles.argtypes = [ctypes.POINTER(ConvDesc), ctypes.POINTER(ConvTileInfo)]
+        L.structadmm_conv_tiles.restype = ctypes.c_int
         L.structadmm_conv_workspace.argtypes = [ctypes.POINTER(ConvDesc)]
         L.structadmm_conv_workspace.restype = ctypes.c_size_t
         L.structadmm_csr.argtypes = [ctypes.POINTER(CsrDesc), _vp]
@@ -385,6 +394,20 @@ def conv_plan(Xp, sizes: CompactSizes, C: int, D: int, stride: int, pad: int) ->
     g = info.groups
     return {"path": list(info.path)[:g], "ksplit": info.ksplit, "space_to_depth": info.space_to_depth,
             "ig_tile": tuple(info.ig_tile), "footprint_tile": tuple(info.footprint_tile)}
+
+
+def conv_tiles(Xp, sizes: CompactSizes, C: int, D: int, stride: int, pad: int) -> dict:
+    """structadmm_conv_tiles: the tile shapes of that plan (host only).
+    "direct_tile": pixels, filters, fetching wavefronts (0: k_conv), slices in
+    LDS, slices within one tap; "footprint_shape": pixels, filters, wavefronts
+    over the pixels, over the filters.  Zeros for a path that no group takes."""
+    N, H, W, Cx = Xp.shape if not isinstance(Xp, tuple) else Xp
+    d = ConvDesc(N, H, W, Cx, C, D, stride, pad, ctypes.pointer(sizes), 16, 16, 16, 16, 16, None, 0)
+    t = ConvTileInfo()
+    _check(lib().structadmm_conv_tiles(ctypes.byref(d), ctypes.byref(t)), "structadmm_conv_tiles")
+    return {"direct_tile": (t.direct_pixels, t.direct_filters, t.direct_fetchers, t.direct_slices, t.direct_one_tap),
+            "footprint_shape": (t.footprint_pixels, t.footprint_filters, t.footprint_pixel_waves,
+                                t.footprint_filter_waves)}
 
 
 def conv_fwd(Xp, Wc, col_ch, col_tap, sizes: CompactSizes, C: int, D: int, stride: int, pad: int,

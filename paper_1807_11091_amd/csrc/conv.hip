@@ -1030,12 +1030,15 @@ int64_t direct_tiles(const int *Ms, int n, int NPQ, int *filters) {
     return *filters == 64 ? t64 : t128;
 }
 
-// One launch for every group of a, by the kernel and tile shape that the time
-// model of conv_tile.hip expects to be fastest: k_conv_tile, or k_conv with
+// Shape of a launch for every group of a: the one that the time model of
+// conv_tile.hip expects to be fastest, or k_conv_tile's for split columns.
+int direct_row(const ConvArgs &a) { return a.ksplit > 1 ? kTileSplit : tile_pick(a); }
+
+// One launch for every group of a in shape `row`: k_conv_tile, or k_conv with
 // eight wavefronts per 128-pixel tile (two rows of four, each 32 pixels by 32
 // or 64 filters) where a layer has few slices and many tiles: its workgroups,
 // two per CU, hide each other's output.
-int run_conv(ConvArgs a, hipStream_t stream) {
+int run_conv(ConvArgs a, int row, hipStream_t stream) {
     if (a.ngroups == 0) return SA_OK;
     for (int i = 0; i < a.ngroups; ++i)
         a.g[i].divRun = make_fastdiv((uint32_t)std::max(1, a.g[i].run));  // a group without columns has run 0
@@ -1043,7 +1046,6 @@ int run_conv(ConvArgs a, hipStream_t stream) {
     a.divCy = make_fastdiv((uint32_t)std::max(1, a.Cy));
     a.divQ = make_fastdiv((uint32_t)a.Q);
     a.divD = make_fastdiv((uint32_t)a.D);
-    const int row = a.ksplit > 1 ? kTileSplit : tile_pick(a);
     switch (row) {
         case kConv128x128: return launch_conv<128, 128, 4, 2>(a, stream);
         case kConv128x64: return launch_conv<128, 64, 4, 2>(a, stream);
@@ -1149,8 +1151,10 @@ struct ConvPlan {
     int pix_bytes[SA_MAX_CONV_GROUPS], nch[SA_MAX_CONV_GROUPS], ch_lo8[SA_MAX_CONV_GROUPS];
     // k_conv_patch launch, when any group takes it (NP x WM wavefronts)
     int TM, TN, NP, WM, patch_bytes, tab_bytes, lds;
-    // the direct groups run on k_ig (16-row filter tiles) instead of k_conv
+    // the direct groups run on k_ig (16-row filter tiles) instead of shape `row`
+    // of k_conv_tile or k_conv (-1: none)
     bool direct_ig;
+    int row;
     // split K (launches that would fill few CUs): chunks, and the binary32
     // partial sums [ksplit][part_stride] at byte part_off of the scratch
     int ksplit;
@@ -1276,6 +1280,29 @@ float patch_time(const PatchShape &t, int64_t pb, int64_t lds, int K, int64_t wg
     return t.factor * (0.7936f + std::sqrt(std::sqrt(a2 * a2 + b2 * b2 + m2 * m2)));
 }
 
+// What the time model reads of the groups that take the direct kernels on the
+// input (or its space-to-depth image).
+ConvArgs direct_model(const sa_conv_desc &d, const sa_compact_sizes &s, const ConvPlan &p) {
+    ConvArgs a;
+    memset(&a, 0, sizeof a);
+    a.ksplit = p.ksplit;
+    a.C = p.s2d_direct ? p.gC : d.C;
+    a.D = p.s2d_direct ? p.gD : d.D;
+    a.W = p.s2d_direct ? p.gW : d.W;
+    a.pad = p.s2d_direct ? 0 : d.pad;
+    a.NPQ = p.NPQ;
+    for (int g = 0; g < s.groups; ++g) {
+        if (p.path[g] != kDirect) continue;
+        ConvGroup &G = a.g[a.ngroups++];
+        G.M = s.M[g];
+        G.ldk = s.ldk[g];
+        G.run = s.run[g];
+        G.Cx = p.s2d_direct ? p.gCx : d.Cx;
+        G.x_bytes = (uint32_t)(p.s2d_direct ? p.s2d_bytes : (size_t)d.N * d.H * d.W * d.Cx * 2);
+    }
+    return a;
+}
+
 // Split K when every group takes the direct kernel (on the input, or on its
 // gathered im2col rows), the launches leave CUs idle and the tiles are long
 // (small batches): the 64-column slices are cut into ksplit chunks (at most 8,
@@ -1288,27 +1315,13 @@ void split_plan(const sa_conv_desc &d, const sa_compact_sizes &s, ConvPlan *pl) 
     p.ksplit = 1;
     int nd = 0, ng = 0, Md[SA_MAX_CONV_GROUPS], Mg[SA_MAX_CONV_GROUPS];
     int min_sl = 1 << 30;
-    ConvArgs a;  // what the time model reads of the direct groups
-    memset(&a, 0, sizeof a);
-    a.C = p.s2d_direct ? p.gC : d.C;
-    a.D = p.s2d_direct ? p.gD : d.D;
-    a.W = p.s2d_direct ? p.gW : d.W;
-    a.pad = p.s2d_direct ? 0 : d.pad;
-    a.NPQ = p.NPQ;
     for (int g = 0; g < s.groups; ++g) {
         if (p.path[g] == kSkip) continue;
         if (p.path[g] == kPatch) return;
-        if (p.path[g] == kDirect) {
+        if (p.path[g] == kDirect)
             Md[nd++] = s.M[g];
-            ConvGroup &G = a.g[a.ngroups++];
-            G.M = s.M[g];
-            G.ldk = s.ldk[g];
-            G.run = s.run[g];
-            G.Cx = p.s2d_direct ? p.gCx : d.Cx;
-            G.x_bytes = (uint32_t)(p.s2d_direct ? p.s2d_bytes : (size_t)d.N * d.H * d.W * d.Cx * 2);
-        } else {  // two-phase: the direct kernel over the gathered rows
+        else  // two-phase: the direct kernel over the gathered rows
             Mg[ng++] = s.M[g];
-        }
         min_sl = std::min(min_sl, s.ldk[g] / kBK);
     }
     if (nd + ng == 0) return;
@@ -1323,6 +1336,7 @@ void split_plan(const sa_conv_desc &d, const sa_compact_sizes &s, ConvPlan *pl) 
     if (most < 2 || (int64_t)min_sl * (most - 1) <= 20 * most) return;
     p.ksplit = most;
     if (ng == 0) {
+        const ConvArgs a = direct_model(d, s, p);
         // The split that the time model expects to be fastest: the second pass
         // at 2 us, or 1 us for 8 chunks (all of them loaded at once), plus the
         // partial sums written and read at 1.6 TB/s.  Fitted on the GPU time of
@@ -1649,6 +1663,11 @@ int conv_plan(const sa_conv_desc &d, ConvPlan *pl) {
     }
     split_plan(d, p.eff, &p);
     direct_plan(p.eff, &p);
+    p.row = -1;
+    if (!p.direct_ig) {
+        const ConvArgs a = direct_model(d, p.eff, p);
+        if (a.ngroups > 0) p.row = direct_row(a);
+    }
     return SA_OK;
 }
 
@@ -1706,6 +1725,26 @@ extern "C" int structadmm_conv_plan(const sa_conv_desc *desc, sa_conv_plan_info 
         info->footprint_tile[2] = p.NP;
     }
     if (!patch && !p.s2d_direct) info->space_to_depth = 0;
+    return SA_OK;
+}
+
+extern "C" int structadmm_conv_tiles(const sa_conv_desc *desc, sa_conv_tile_info *info) {
+    clear_error();
+    if (!desc || !info) return fail(SA_E_ARG, "conv_tiles: desc and info are required");
+    ConvPlan p;
+    if (int rc = conv_plan(*desc, &p)) return rc;
+    memset(info, 0, sizeof *info);
+    if (p.row >= 0) {
+        tile_shape(p.row, &info->direct_pixels, &info->direct_filters, &info->direct_fetchers, &info->direct_slices);
+        info->direct_one_tap = info->direct_fetchers > 0 && tile_one_tap(direct_model(*desc, p.eff, p));
+    }
+    for (int g = 0; g < desc->sizes->groups; ++g) {
+        if (p.path[g] != kPatch) continue;
+        info->footprint_pixels = 32 * p.NP * p.TN;
+        info->footprint_filters = 32 * p.TM * p.WM;
+        info->footprint_pixel_waves = p.NP;
+        info->footprint_filter_waves = p.WM;
+    }
     return SA_OK;
 }
 
@@ -1955,7 +1994,7 @@ extern "C" int structadmm_conv_fwd(const sa_conv_desc *desc, hipStream_t stream)
             G.o_off = c.o_off;
         }
         if (int rc = ig_run(ia, -1, stream)) return rc;
-    } else if (int rc = run_conv(direct, stream)) {
+    } else if (int rc = run_conv(direct, p.row, stream)) {
         return rc;
     }
     if (pa.ngroups > 0) {
@@ -1963,7 +2002,9 @@ extern "C" int structadmm_conv_fwd(const sa_conv_desc *desc, hipStream_t stream)
         if (!shape) return fail(SA_E_ARG, "conv: no tile shape for the gathered groups");
         if (int rc = shape->launch(pa, p.lds, stream)) return rc;
     }
-    if (int rc = run_conv(gathered, stream)) return rc;
+    if (gathered.ngroups > 0) {
+        if (int rc = run_conv(gathered, direct_row(gathered), stream)) return rc;
+    }
     if (p.ksplit > 1) {
         const int64_t total = (int64_t)NPQ * p.Cy;
         const int64_t blocks = (total + 1023) / 1024;

@@ -21,6 +21,11 @@ constexpr int kConv128x64 = 8;   // k_conv, 128 pixels x 64 filters
 float tile_time(const ConvArgs &a, int row, int ksplit, int64_t cus);
 // The fastest shape by that model.
 int tile_pick(const ConvArgs &a);
+// Pixels and filters of a tile of shape `row`, its fetching wavefronts (0:
+// k_conv) and the slices that its LDS holds.
+void tile_shape(int row, int *pixels, int *filters, int *fetchers, int *slices);
+// Does every slice of 64 columns lie in one tap?
+bool tile_one_tap(const ConvArgs &a);
 // Launches every group of a with k_conv_tile shape `row` < kTileShapes (with
 // a.ksplit > 1: kTileSplit, binary32 partial sums).
 int tile_run(const ConvArgs &a, int row, hipStream_t stream);

@@ -598,18 +598,51 @@ int tile_pick(const ConvArgs &a) {
     return best;
 }
 
-int tile_run(const ConvArgs &a, int row, hipStream_t stream) {
-    if (a.ksplit > 1) return launch<64, 64, 2, 2, 4, 32, true>(a, stream);
+namespace {
+// k_conv_tile's shapes: calls f with the template arguments of shape `row`
+template <int BM, int BN, int WN, int WM, int S, int MI>
+struct Shape {
+    using Cfg = TileCfg<BM, BN, WN, WM, S, MI>;
+    static constexpr int pixels = BM, filters = BN, slices = S;
+    static int run(const ConvArgs &a, hipStream_t stream) { return launch<BM, BN, WN, WM, S, MI, false>(a, stream); }
+};
+template <typename F>
+int with_shape(int row, F f) {
     switch (row) {
-        case 0: return launch<64, 64, 2, 2, 4, 32, false>(a, stream);
-        case 1: return launch<128, 48, 4, 1, 2, 16, false>(a, stream);
-        case 2: return launch<128, 80, 4, 1, 2, 16, false>(a, stream);
-        case 3: return launch<64, 160, 2, 2, 3, 16, false>(a, stream);
-        case 4: return launch<64, 160, 2, 2, 2, 16, false>(a, stream);
-        case 5: return launch<128, 128, 2, 2, 3, 16, false>(a, stream);
-        case 6: return launch<64, 128, 2, 2, 2, 32, false>(a, stream);
+        case 0: return f(Shape<64, 64, 2, 2, 4, 32>());
+        case 1: return f(Shape<128, 48, 4, 1, 2, 16>());
+        case 2: return f(Shape<128, 80, 4, 1, 2, 16>());
+        case 3: return f(Shape<64, 160, 2, 2, 3, 16>());
+        case 4: return f(Shape<64, 160, 2, 2, 2, 16>());
+        case 5: return f(Shape<128, 128, 2, 2, 3, 16>());
+        case 6: return f(Shape<64, 128, 2, 2, 2, 32>());
         default: return fail(SA_E_ARG, "conv: unknown tile shape %d", row);
     }
+}
+}  // namespace
+
+void tile_shape(int row, int *pixels, int *filters, int *fetchers, int *slices) {
+    if (row >= kTileShapes) {
+        *pixels = 128;
+        *filters = row == kConv128x64 ? 64 : 128;
+        *fetchers = 0;
+        *slices = 2;
+        return;
+    }
+    (void)with_shape(row, [&](auto shape) {
+        *pixels = shape.pixels;
+        *filters = shape.filters;
+        *fetchers = decltype(shape)::Cfg::PW;
+        *slices = shape.slices;
+        return SA_OK;
+    });
+}
+
+bool tile_one_tap(const ConvArgs &a) { return uniform_taps(a); }
+
+int tile_run(const ConvArgs &a, int row, hipStream_t stream) {
+    if (a.ksplit > 1) return launch<64, 64, 2, 2, 4, 32, true>(a, stream);
+    return with_shape(row, [&](auto shape) { return shape.run(a, stream); });
 }
 
 }  // namespace sa

@@ -51,6 +51,7 @@ def _c_layout():
         "sa_conv_desc": ("ConvDesc", ["N", "pad", "sizes", "X", "Y", "ws", "ws_bytes", "ldy"]),
         "sa_conv_plan_info": ("ConvPlanInfo", ["groups", "path", "ksplit", "space_to_depth", "ig_tile",
                                                "footprint_tile"]),
+        "sa_conv_tile_info": ("ConvTileInfo", [f for f, _ in sa.ConvTileInfo._fields_]),
         "sa_csr_desc": ("CsrDesc", ["A", "D", "nnz", "Z", "kept_idx", "row_ptr", "col", "val"]),
         "sa_sparse_conv_desc": ("SparseConvDesc", ["N", "Cx", "A", "D", "groups", "stride", "pad", "nnz", "X",
                                                    "row_ptr", "col", "val", "Y", "ws", "ws_bytes",

@@ -105,7 +105,7 @@ def conv_case(N, Cin, H, Wd, A, C, D, stride, pad, groups, kind, keep, seed, den
     Xb = oracle.pack(X)
     assert bitwise_equal(Xp.cpu().numpy(), Xb.transpose(0, 2, 3, 1))
     if expect is not None:  # the kernel the case is meant to exercise
-        plan = sa.conv_plan(Xp, sizes, C, D, stride, pad)
+        plan = {**sa.conv_plan(Xp, sizes, C, D, stride, pad), **sa.conv_tiles(Xp, sizes, C, D, stride, pad)}
         for key, want in expect.items():
             got = plan[key] if key != "path" else set(plan["path"]) - {sa.CONV_NONE}
             assert got == want, (key, got, want, plan)
