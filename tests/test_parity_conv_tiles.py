@@ -49,6 +49,25 @@ CASES = [
     ((16, 24, 28, 28, 154, 1, 1, 1, 0, 1, sa.FILTER, 1.0), T(64, 160, 3, 0)),
     ((15, 72, 32, 32, 300, 1, 1, 1, 0, 1, sa.FILTER, 1.0), T(64, 160, 2, 0)),
     ((25, 72, 28, 28, 100, 3, 3, 1, 1, 1, sa.FILTER, 1.0), T(128, 128, 3, 0)),
+    # every shape over several conv groups, mostly with more tiles than the GPU
+    # holds workgroups (a workgroup's range then runs on from group to group),
+    # for slices within one tap and across taps; at least 40 columns, for the
+    # reason given at FOOTPRINT (8 columns: 13 times the RMS, 0.026 by rounding alone)
+    ((38, 576, 17, 17, 24, 1, 1, 1, 0, 3, sa.FILTER, 1.0), T(64, 64, 4, 1)),
+    ((22, 216, 32, 31, 60, 1, 1, 1, 0, 3, sa.FILTER, 1.0), T(64, 64, 4, 0)),
+    ((57, 256, 28, 29, 76, 1, 1, 1, 0, 2, sa.FILTER, 1.0), T(128, 48, 2, 1)),
+    ((78, 200, 32, 32, 8, 3, 3, 1, 0, 1, sa.FILTER, 1.0), T(128, 48, 2, 0)),
+    ((147, 400, 17, 17, 16, 3, 3, 1, 0, 2, sa.FILTER, 1.0), T(128, 48, 2, 0)),
+    ((39, 256, 32, 33, 130, 1, 1, 1, 0, 2, sa.FILTER, 1.0), T(128, 80, 2, 1)),
+    ((53, 120, 40, 41, 195, 1, 1, 2, 0, 3, sa.FILTER, 1.0), T(128, 80, 2, 0)),
+    ((49, 192, 32, 32, 390, 3, 3, 2, 0, 3, sa.FILTER, 1.0), T(64, 160, 3, 1)),
+    ((9, 120, 20, 20, 390, 1, 1, 1, 0, 3, sa.FILTER, 1.0), T(64, 160, 3, 0)),
+    ((21, 128, 56, 55, 260, 1, 1, 2, 0, 2, sa.FILTER, 1.0), T(64, 160, 2, 1)),
+    ((22, 80, 31, 32, 260, 1, 1, 1, 0, 2, sa.FILTER, 1.0), T(64, 160, 2, 0)),
+    ((55, 192, 20, 20, 288, 3, 3, 2, 1, 3, sa.FILTER, 1.0), T(128, 128, 3, 1)),
+    ((98, 320, 32, 32, 176, 3, 3, 2, 1, 2, sa.FILTER, 1.0), T(128, 128, 3, 0)),
+    ((10, 128, 40, 41, 192, 1, 1, 1, 0, 2, sa.FILTER, 1.0), T(64, 128, 2, 1)),
+    ((22, 144, 31, 32, 195, 1, 1, 1, 0, 3, sa.FILTER, 1.0), T(64, 128, 2, 0)),
     ((4, 512, 7, 7, 77, 3, 3, 1, 1, 1, sa.FILTER, 1.0), D),  # 72 slices
     ((1, 512, 7, 7, 33, 3, 3, 1, 1, 1, sa.FILTER, 1.0), {"path": {sa.CONV_DIRECT}, "ksplit": 8}),
     ((1, 704, 9, 8, 50, 3, 3, 1, 1, 2, sa.FILTER, 0.6), {"path": {sa.CONV_DIRECT}, "ksplit": 8}),  # runs of 352, split
