@@ -3,8 +3,8 @@
 //
 // Per conv group g the GEMM is  Y^T[m, px] = sum_k Wc_g[m, k] * Xcol[px, k]
 // with px = (n, p, q) an output pixel and k a kept (tap, channel) column.
-// structadmm_conv_fwd takes one of three paths per group, all on MFMA
-// bf16 MFMAs (A = Wc rows, B = output pixels, fp32 accumulate):
+// structadmm_conv_fwd takes one of three paths per group, all on bf16 MFMAs
+// (A = Wc rows, B = output pixels, fp32 accumulate):
 //
 // direct: the group's columns are every tap times one run of 8k input channels
 //   (dense, filter- or channel-pruned layers).  Most layers run k_conv_tile
@@ -1361,16 +1361,21 @@ void split_plan(const sa_conv_desc &d, const sa_compact_sizes &s, ConvPlan *pl) 
     p.ws_need = p.part_off + ((size_t)p.ksplit * p.part_stride * 4 + 255) / 256 * 256;
 }
 
-// Kernel for the groups read straight from the NHWC input (measured on
-// gfx950 over the ResNet-50 and AlexNet layers, in isolation and inside a
-// block of layers whose inputs come cold from HBM): k_ig, whose filter tiles
-// grow in steps of 16, for groups of at most 64 kept filters that k_conv's
+// Kernel for the groups read straight from the NHWC input: k_ig, whose filter
+// tiles grow in steps of 16, for groups of at most 64 kept filters that k_conv's
 // 64-filter tiles would pad by 15% or more, over 384-512 columns and at least
-// 2^16 pixels (AlexNet's first layer of 48 kept filters on its space-to-depth
-// image: 62 vs 68 us); the eight-wavefront k_conv tiles otherwise (k_ig was
-// 3-25% slower on every other layer tried, among them ResNet-50's 1x1 layers
-// of 38 and 77 kept filters and its first layer).  Not for split K over
-// workgroups (small batches).
+// 2^16 pixels; otherwise the time model's choice of k_conv_tile's and k_conv's
+// shapes.  Not for split K over workgroups (small batches).  The bounds come
+// from comparing k_ig with k_conv alone over the ResNet-50 and AlexNet layers
+// (k_ig was 3-25% slower on every other layer tried).  Within them, against the
+// model's choice, where slices run on from tap to tap (that choice is k_conv):
+// AlexNet's first layer of 48 kept filters on its space-to-depth image, batch
+// 128, 60-63 vs 65-66 us; [24, 16, 5, 5] on 55x55, batch 128, 33 vs 37;
+// [40, 56, 3, 3] on 56x56, batch 24, 12.6 vs 13.0; [33, 48, 3, 3], batch 32,
+// 14.6 both.  Where every slice lies in one tap, k_conv_tile's 48-filter tiles
+// are the faster ones and the rule does not know it: [38, 448, 1, 1] on 56x56,
+// batch 64, 41 vs 31; [48, 512, 1, 1] 43 vs 35; [20, 384, 1, 1], batch 32, 19.4
+// vs 16.1.
 void direct_plan(const sa_compact_sizes &s, ConvPlan *pl) {
     ConvPlan &p = *pl;
     p.direct_ig = false;
@@ -1407,8 +1412,10 @@ int tile_rows(const ConvPlan &p, int frags, int (&rows)[9]) {
 // over the 422 measured layers the choice takes 0.92 of the former one's time, and
 // none runs over 2% slower.  `open`: the fit covers the layer (strided
 // few-channel layers on a space-to-depth image are not in it).  Tiles of more
-// than 128 pixels are left to the rules before it (choosing them here too would
-// take 0.91).
+// than 128 pixels are left to the rules before it: choosing them here too would
+// take 0.91, a gain far within the model's scatter, and would move a layer whose
+// shape the parity tests state ([128, 16, 3, 3] on 13x13, batch 400) from
+// 128-pixel to 256-pixel tiles.
 void patch_retile(const sa_compact_sizes &s, bool open, int (&rows)[9], ConvPlan *pl) {
     ConvPlan &p = *pl;
     if (!open) return;

@@ -1,8 +1,8 @@
 // gfx950 direct CONV (implicit GEMM) over a group's compacted matrix: every tap
 // of one run of 8k input channels, read straight from the NHWC input.
 //
-// k_conv_tile: persistent workgroups of four or eight MFMA wavefronts
-// (consumers) and four fetching wavefronts (producers).  Operands travel in
+// k_conv_tile: persistent workgroups of four MFMA wavefronts (consumers) and
+// four fetching wavefronts (producers).  Operands travel in
 // slices of 64 columns through a ring of S LDS buffers: a producer's
 // buffer_load ... lds writes 16 bytes per lane (8 rows of 128 bytes per
 // instruction) straight into LDS, S slices ahead and across tile boundaries,

@@ -545,10 +545,13 @@ int sp_plan(const sa_sparse_conv_desc &d, SpPlan *p) {
     // The dense product multiplies the zeros too, at the matrix cores' rate:
     // worth it from a density up that depends on how well the layer fills them.
     // k_conv_tile's model and the guard's read of the output stand against the
-    // gathers at 10.5 million inputs per microsecond (measured: 4 to 10, up to
-    // 16 with few channels).  Of 120 random layers (1 to 256 images, 7x7 to
-    // 56x56, 8 to 512 channels, 3 to 40% kept) the rule takes 18, all 2.2 to 16
-    // times faster than the gathers.
+    // gathers at 10.5 million inputs per microsecond.  That is above what most
+    // layers' gathers reach (4 to 10 measured, up to 16 with few channels), so
+    // the line lies on the gathers' side: of 120 random layers (1 to 256 images,
+    // 7x7 to 56x56, 8 to 512 channels, 3 to 40% kept) the rule takes 18, all 2.2
+    // to 16 times faster than the gathers, and some it leaves would gain too
+    // (the 256-channel 3x3 layer on 14x14 at batch 256, 2.5% kept: 101 us by
+    // gathers, about 75 by the dense product and its guard).
     p->ldk = (int)round_up(K, kBK);
     p->dense = false;
     p->ws_dense = p->ws_need;
