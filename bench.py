@@ -227,7 +227,7 @@ def run_step(torch, sa, wl, layers, ws, cws, ev, record):
             o.flops_c = 2 * wl.batch * L.P * L.Q * sum(sizes.M[g] * kept_k(sizes, g) for g in range(sizes.groups))
             o.flops_d = 2 * wl.batch * L.P * L.Q * sum(sized.M[g] * kept_k(sized, g) for g in range(sized.groups))
             o.sizes_c = sizes
-            o.plan_c = sa.conv_plan(o.Xp, sizes, L.C, L.D, L.stride, L.pad)
+            o.plan_c = plan_of(sa, o.Xp, sizes, L)
         # scratch for groups whose im2col rows are gathered first; the kept
         # columns move between ADMM steps, so it is sized for every step (outside
         # the CONV events) and grown when a step needs more
@@ -349,7 +349,7 @@ def conv_only(args):
             o.Xp = sa.pack_nhwc(o.X, keep=inm)
         else:
             sa.pack_nhwc(o.X, out=o.Xp)
-        plan = sa.conv_plan(o.Xp, sizes, L.C, L.D, L.stride, L.pad)
+        plan = plan_of(sa, o.Xp, sizes, L)
         kern = kernel_of(sa, plan)
         if args.kernel is not None and kern != args.kernel:
             continue
@@ -568,13 +568,23 @@ def _sparse_vs_dense(torch, sa, L, Xp, X, dW, Z, csr, k):
     N = X.shape[0]
     products = N * L.P * L.Q * k
     best = min(td["median_ms"], tm["median_ms"])
+    # the route: a scratch larger than the padded entries' arrays (row starts,
+    # offsets, values) holds the dense matrix, which the matrix cores multiply
+    up = lambda n: (n + 255) // 256 * 256
+    cap = (k + 7 * shape[0] + 7) // 8 * 8
+    dense = need > up((shape[0] + 1) * 4) + up(cap * 4) + up(cap * 2)
+    if dense:
+        rate = {"route": "dense product on the matrix cores",
+                "mfma_frac": round(2 * N * L.P * L.Q * dW.numel() / (ts["median_ms"] * 1e-3) / 1e12 / BF16_PEAK_TFLOPS, 4)}
+    else:
+        rate = {"route": "gathers",
+                "lds_gather_frac": round(products / (ts["median_ms"] * 1e-3) / LDS_GATHER_PEAK_PRODUCTS, 4)}
     return {"kept": k, "density_pct": round(100.0 * k / dW.numel(), 3),
             "sparse_us": round(ts["median_ms"] * 1e3, 2), "sparse_with_prep_us": round(tsf["median_ms"] * 1e3, 2),
             "dense_us": round(td["median_ms"] * 1e3, 2),
             "miopen_dense_us": round(tm["median_ms"] * 1e3, 2),
             "speedup_vs_best_dense": round(best / ts["median_ms"], 3),
-            "sparse_useful_tflops": round(2 * products / (ts["median_ms"] * 1e-3) / 1e12, 2),
-            "lds_gather_frac": round(products / (ts["median_ms"] * 1e-3) / LDS_GATHER_PEAK_PRODUCTS, 4)}
+            "sparse_useful_tflops": round(2 * products / (ts["median_ms"] * 1e-3) / 1e12, 2), **rate}
 
 
 def suite_sparse(torch, sa):
@@ -1002,7 +1012,14 @@ def progress(msg):
 
 
 # source file of each CONV kernel (its profile summaries hold that file's hash)
-KERNEL_SOURCE = {"k_conv": "conv.hip", "k_conv_patch": "conv.hip", "k_ig": "conv_ig.hip"}
+KERNEL_SOURCE = {"k_conv_tile": "conv_tile.hip", "k_conv": "conv.hip", "k_conv_patch": "conv.hip",
+                 "k_ig": "conv_ig.hip"}
+
+
+def plan_of(sa, Xp, sizes, L):
+    """The library's plan of a CONV: kernel path of each group and tile shapes."""
+    return {**sa.conv_plan(Xp, sizes, L.C, L.D, L.stride, L.pad),
+            **sa.conv_tiles(Xp, sizes, L.C, L.D, L.stride, L.pad)}
 
 
 def kernel_of(sa, plan):
@@ -1013,8 +1030,8 @@ def kernel_of(sa, plan):
     if len(paths) != 1 or plan["ksplit"] > 1 or plan["space_to_depth"]:
         return None
     p = paths.pop()
-    if p == sa.CONV_DIRECT:
-        return "k_conv"
+    if p == sa.CONV_DIRECT:  # k_conv_tile has wavefronts that only fetch
+        return "k_conv_tile" if plan["direct_tile"][2] else "k_conv"
     if p == sa.CONV_DIRECT_IG:
         return "k_ig"
     if p == sa.CONV_FOOTPRINT:
