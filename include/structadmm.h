@@ -322,8 +322,10 @@ typedef struct sa_conv_desc {
 } sa_conv_desc;
 
 /* Scratch bytes structadmm_conv_fwd needs.  None when the input has a
- * multiple of 8 channels and each group's input footprint fits in LDS (any
- * column set).  An input with other channel counts is first rewritten as its
+ * multiple of 8 channels, each group's input footprint fits in LDS (any
+ * column set) and the columns are not split over workgroups (a launch of few
+ * tiles: structadmm_conv_plan's ksplit > 1 keeps that many binary32 copies of
+ * the output).  An input with other channel counts is first rewritten as its
  * space-to-depth image (bfloat16, channels padded to a multiple of 8) in the
  * scratch; a group whose footprint does not fit in LDS first gathers its
  * compacted im2col rows, N*P*Q x ldk bfloat16, into a region of its own.
